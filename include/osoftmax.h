@@ -103,8 +103,11 @@ enum osm_kernel {
     OSM_KERNEL_ROWS = 1,  /* param = lanes per row.  Softmax: 4, 8, 16, 32
                              (several rows per wavefront), 64 (a row per
                              wavefront) or 128, 256, 512, 1024 (a row per
-                             workgroup).  Top-k: 64, 128 or 256 (one, two or
-                             four wavefronts per row). */
+                             workgroup).  Top-k: 64 or 128 (one or two
+                             wavefronts per row) or 256 (a workgroup per row:
+                             four wavefronts, or eight for rows of 4097 to
+                             8192 whole 16-byte vectors, which eight hold in
+                             registers). */
     OSM_KERNEL_SPLIT = 2  /* param = chunks per row S >= 1: a workgroup per
                              chunk; per-chunk normalizer pairs (and, for
                              top-k, per-chunk top-k keys) go through a
@@ -180,7 +183,7 @@ OSM_API int softmax_topk_dt(const void* x, float* vals, int32_t* idx, int64_t N,
 
 /* softmax_topk_dt with an explicit kernel: OSM_KERNEL_AUTO (what
  * softmax_topk_dt uses; param ignored), OSM_KERNEL_ROWS with param = lanes
- * per row: 64, 128 or 256 (one, two or four wavefronts per row), or
+ * per row: 64, 128 or 256 (one or two wavefronts, or a workgroup per row), or
  * OSM_KERNEL_SPLIT with param = chunks per row (clamped so that every chunk
  * starts inside the row).  Indices are identical across kernels; vals agree
  * within binary32 rounding of the reduction tree.

@@ -328,7 +328,10 @@ int run_softmax(const void* x, void* y, int64_t N, int64_t V, int dtype, int mod
     return hip_status(f);
 }
 
-// Top-k plan: one wavefront per row once the batch alone can give every
+// Top-k plans.  Rows that the registers hold (topk_held.hpp) take a wavefront
+// or a workgroup each; only longer ones are streamed or split.
+
+// Streamed rows: one wavefront per row once the batch alone can give every
 // SIMD several wavefronts, or when rows are short (up to 1536 elements: a
 // wavefront streams them in a step or two, and more wavefronts per row only
 // add the barrier and the cross-wavefront merge); a small batch of long rows
@@ -342,13 +345,13 @@ int run_softmax(const void* x, void* y, int64_t N, int64_t V, int dtype, int mod
 // The chunk count is also capped so that a row's S * K partial keys fit the
 // merge's single register batch (512 keys; a larger merge goes through the
 // queue and its repeated selections: 4 x 10^6 top-5 took 20.8 us at 128
-// chunks against 15.7 at 52).
-Plan choose_topk(int64_t N, int64_t V, int K, int cus) {
+// chunks against 15.7 at 52), and chunks keep at least `min_chunk` elements.
+Plan choose_topk_stream(int64_t N, int64_t V, int K, int cus, int64_t min_chunk = 4096) {
     if (N >= 4 * (int64_t)cus || V <= 1536) return {OSM_KERNEL_ROWS, 64};
     if (N < 2 * (int64_t)cus && V >= 8192) {
         int64_t S = (2 * (int64_t)cus) / N;
         if (S < 2) S = 2;
-        int64_t s_cap = V / 4096;  // keep chunks >= 4096 elements
+        int64_t s_cap = V / min_chunk;
         if (S > s_cap) S = s_cap;
         const int64_t k_cap = 512 / K;
         if (S > k_cap) S = k_cap;
@@ -357,14 +360,46 @@ Plan choose_topk(int64_t N, int64_t V, int K, int cus) {
     return {OSM_KERNEL_ROWS, 256};
 }
 
+// Rows of nv 16-byte vectors, by the measured crossings (us, one device):
+//  * up to 1024 vectors a wavefront holds a row.  It is the faster one for
+//    large batches (16000 x 4000 bfloat16 top-5: 25.6 against 38.4 with a
+//    workgroup per row; 4000 x 1000 binary32 6.4 against 8.0); for batches
+//    under four rows a CU, rows past 1536 elements take a workgroup
+//    (300 x 2000 binary32 top-5: 4.4 against 5.1);
+//  * up to 8192 vectors a workgroup of four (to 4096 vectors) or eight
+//    wavefronts does, against streaming the row by one wavefront (4000 x 10000
+//    binary32 top-5 / top-50: 28.2 / 29.7 against 31.0 / 37.2; 4000 x 32000
+//    bfloat16 43.3 / 46.7 against 52.4 / 67.8; 16000 x 32000 binary32 292 / 328
+//    against 303 / 330) and against splitting it (64 x 32000 binary32 8.3 / 9.9
+//    against 9.8 / 11.4).  Large batches of bfloat16 rows past 4096 vectors
+//    stream (4000 x 50000 top-5: 69.1 against 73.9: half the bytes for the same
+//    arithmetic, which a held row does not overlap with its loads), and a few
+//    rows past 4096 vectors at small K split (1 x 65000 bfloat16 top-5: 6.9
+//    against 8.0; top-50 9.9 against 9.3);
+//  * longer rows are streamed or split, the chunks with at least 2048 vectors
+//    (16 x 128256 bfloat16 top-5: 9.4 in 8 chunks, 12.4 in 31), or 1024 for a
+//    few rows (1 x 128256 bfloat16 top-5: 8.2 in 7 chunks, 7.1 in 31).
+Plan choose_topk(int64_t N, int64_t V, int dtype, int K, int cus) {
+    const int64_t E = elems_per_vec(dtype), nv = V / E;
+    const bool many = N >= 4 * (int64_t)cus;
+    if (V <= 1536 || (many && nv <= 1024)) return {OSM_KERNEL_ROWS, 64};
+    if (nv <= 4096) return {OSM_KERNEL_ROWS, 256};
+    if (nv <= 8192 && (many ? dtype == OSM_F32 || N < 8 * (int64_t)cus : N >= 16 || K > 8))
+        return {OSM_KERNEL_ROWS, 256};
+    return choose_topk_stream(N, V, K, cus, (N <= 8 ? 1024 : 2048) * E);
+}
+
 // One top-k pass of variant `var` over x (already validated).  noalloc: the
 // split path's partials and row counters go to the device's fixed scratch
 // array instead of the stream's pool buffers.
 int launch_topk_pass(const void* x, float* vals, int32_t* idx, int64_t N, int64_t V, int K,
                      int dtype, int var, int kernel, int64_t param, DeviceState* ds,
                      hipStream_t stream, bool noalloc = false) {
-    Plan p = kernel == OSM_KERNEL_AUTO ? choose_topk(N, V, K, ds->cus) : Plan{kernel, param};
-    osm::TopkLaunch a{x, vals, idx, nullptr, N, V, K, 1, 1, V, stream};
+    // (the safe variant reads its rows twice and is always streamed)
+    Plan p = kernel != OSM_KERNEL_AUTO ? Plan{kernel, param}
+             : var == osm::TK_SAFE     ? choose_topk_stream(N, V, K, ds->cus)
+                                       : choose_topk(N, V, dtype, K, ds->cus);
+    osm::TopkLaunch a{x, vals, idx, nullptr, N, V, K, 1, 1, V, ds->cus, stream};
     if (p.kernel == OSM_KERNEL_ROWS) {
         a.waves_per_row = (int)(p.param / 64);
         return hip_status(osm::launch_topk(a, dtype, var));
@@ -589,7 +624,7 @@ int osm_topk_plan(int64_t N, int64_t V, int dtype, int K, int* kernel, int64_t* 
     if (K < 1 || K > OSM_TOPK_KMAX || (int64_t)K > V) return OSM_EINVAL;
     if (!kernel || !param) return OSM_EINVAL;
     DeviceState* ds = device_state(nullptr);
-    Plan p = choose_topk(N, V, K, ds ? ds->cus : 256);
+    Plan p = choose_topk(N, V, dtype, K, ds ? ds->cus : 256);
     *kernel = p.kernel;
     *param = p.param;
     return OSM_OK;

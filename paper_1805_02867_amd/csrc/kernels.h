@@ -65,6 +65,7 @@ struct TopkLaunch {
     int K;
     int waves_per_row;   // S <= 1: 1, 2 (TK_ONLINE only) or 4
     int64_t S, chunk;    // chunks per row and their length in elements (S > 1)
+    int cus;             // compute units of the device
     hipStream_t st;
     // S > 1: N zeroed per-row counters, so that each row's last chunk merges
     // the row in the same kernel (the counters are left zeroed); null: a

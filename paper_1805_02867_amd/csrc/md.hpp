@@ -74,6 +74,12 @@ __device__ __forceinline__ void out_vals(float (&v)[N], float S, float rd) {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// Keep `q` in its registers as-is and make the compiler forget what it
+// derived from it, so that each phase widens the packed elements again
+// instead of keeping a widened copy live across the phases (for bfloat16
+// that copy would need twice the registers).
+__device__ __forceinline__ void opaque(u32x4& q) { asm volatile("" : "+v"(q)); }
+
 // A 16-byte vector: 4 binary32 or 8 bfloat16 elements.
 template <typename T> struct Vec;
 

@@ -42,12 +42,6 @@ __device__ __forceinline__ void widen_vec(u32x4 q, float (&x)[Vec<T>::N]) {
     }
 }
 
-// Keep `q` in its registers as-is and make the compiler forget what it
-// derived from it, so that each phase widens the packed elements again
-// instead of keeping a widened copy live across the phases (for bfloat16
-// that copy would need twice the registers).
-__device__ __forceinline__ void opaque(u32x4& q) { asm volatile("" : "+v"(q)); }
-
 template <typename T, int BLOCK, int R, bool YVEC>
 __global__ __launch_bounds__(BLOCK) void softmax_resident(const T* __restrict__ x,
                                                          T* __restrict__ y, int64_t N,

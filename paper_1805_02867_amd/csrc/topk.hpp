@@ -42,6 +42,9 @@
 //    several wavefronts per row, wavefront 0 first selects the K largest keys
 //    of their lists.
 //
+// These kernels stream rows that do not fit in registers (topk_held.hpp has
+// the others) and every row of the safe variant.
+//
 // Three shapes: one, two or four wavefronts per row (four, two or one rows
 // per 256-thread workgroup).  Fewer wavefronts per row keep a row's filter
 // state in fewer hands (one wavefront needs no barrier at all); more give
@@ -127,7 +130,7 @@ __device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
 
 // ----------------------------------------------------------------- sorting
 // Value of lane (lane ^ J) for the sorting networks: DPP quad permutations
-// for 1 and 2, the LDS-crossbar swizzle for 4 and 8, and for 16 and 32 the
+// for 1 and 2, DPP mirrors and rotations for 4 and 8, and for 16 and 32 the
 // operand of the permlane swap pair that came from the other row / half
 // (after a 16-lane swap, lanes of even rows hold their partner's value in
 // the second result and lanes of odd rows in the first; likewise for the
@@ -138,8 +141,11 @@ __device__ __forceinline__ uint32_t xor_partner(uint32_t v) {
         return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
     } else if constexpr (J == 2) {
         return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
-    } else if constexpr (J == 4 || J == 8) {
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (J << 10) | 0x1F);
+    } else if constexpr (J == 4) {  // xor 7 (half mirror), then xor 3 (quad reversal)
+        const int h = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, h, 0x1B, 0xF, 0xF, false);
+    } else if constexpr (J == 8) {  // a rotation by 8 within 16 lanes
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);
     } else if constexpr (J == 16) {
         auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
         return (__lane_id() & 16) ? p[0] : p[1];
@@ -1007,58 +1013,6 @@ constexpr int topk_unroll() {
     if constexpr (W == 1) return std::is_same<T, float>::value ? OSM_TOPK_U1 : OSM_TOPK_U1B;
     else if constexpr (W == 2) return std::is_same<T, float>::value ? OSM_TOPK_U2 : OSM_TOPK_U1B;
     else return OSM_TOPK_U4;
-}
-
-// Launch of one variant for one element type (see TopkLaunch).
-template <typename T, int VAR>
-hipError_t launch_topk_t(const TopkLaunch& a) {
-    dim3 block(TK_BLOCK);
-    const T* x = static_cast<const T*>(a.x);
-    if (a.S <= 1) {
-        if (a.waves_per_row == 1) {
-            constexpr int RB = TK_BLOCK / 64;
-            dim3 grid((unsigned)((a.N + RB - 1) / RB));
-            hipLaunchKernelGGL((topk_fused<T, 1, topk_unroll<T, 1>(), VAR, false>), grid, block, 0,
-                               a.st, x, a.vals, a.idx, nullptr, nullptr, a.N, a.V, a.K, a.V,
-                               (int64_t)1);
-        } else if (a.waves_per_row == 2) {
-            if constexpr (VAR == TK_ONLINE) {  // the two-wavefront shape is built for Alg. 4 only
-                constexpr int RB = TK_BLOCK / 128;
-                dim3 grid((unsigned)((a.N + RB - 1) / RB));
-                hipLaunchKernelGGL((topk_fused<T, 2, topk_unroll<T, 2>(), VAR, false>), grid,
-                                   block, 0, a.st, x, a.vals, a.idx, nullptr, nullptr, a.N, a.V,
-                                   a.K, a.V, (int64_t)1);
-            } else {
-                return hipErrorInvalidValue;
-            }
-        } else if (a.waves_per_row == 4) {
-            dim3 grid((unsigned)a.N);
-            hipLaunchKernelGGL((topk_fused<T, 4, topk_unroll<T, 4>(), VAR, false>), grid, block, 0,
-                               a.st, x, a.vals, a.idx, nullptr, nullptr, a.N, a.V, a.K, a.V,
-                               (int64_t)1);
-        } else {
-            return hipErrorInvalidValue;
-        }
-        return hipGetLastError();
-    }
-    // split: chunks of a.chunk elements, one workgroup (four wavefronts) each
-    uint64_t* pkeys = static_cast<uint64_t*>(a.part);
-    MD* pmd = reinterpret_cast<MD*>(pkeys + a.N * a.S * a.K);
-    dim3 grid((unsigned)(a.N * a.S));
-    if (a.ctr) {  // merge by each row's last chunk, in the same kernel
-        hipLaunchKernelGGL((topk_split1<T, topk_split_unroll(), VAR>), grid, block, 0, a.st, x,
-                           a.vals, a.idx, pkeys, pmd, a.ctr, a.N, a.V, a.K, a.chunk, a.S);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((topk_fused<T, 4, topk_split_unroll(), VAR, true>), grid, block, 0, a.st,
-                       x, nullptr, nullptr, pkeys, pmd, a.N, a.V, a.K, a.chunk, a.S);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    constexpr int WB = TK_BLOCK / 64;
-    dim3 mgrid((unsigned)((a.N + WB - 1) / WB));
-    hipLaunchKernelGGL((topk_merge<VAR>), mgrid, block, 0, a.st, pkeys, pmd, a.vals, a.idx, a.N,
-                       a.S, a.K);
-    return hipGetLastError();
 }
 
 }  // namespace osm
