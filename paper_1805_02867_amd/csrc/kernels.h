@@ -67,9 +67,8 @@ struct TopkLaunch {
     int64_t S, chunk;    // chunks per row and their length in elements (S > 1)
     int cus;             // compute units of the device
     hipStream_t st;
-    // S > 1: N zeroed per-row counters, so that each row's last chunk merges
-    // the row in the same kernel (the counters are left zeroed); null: a
-    // second kernel merges.
+    // S > 1: N zeroed per-row counters; each row's last chunk merges the row
+    // in the same kernel, and the counters are left zeroed.
     uint32_t* ctr = nullptr;
 };
 

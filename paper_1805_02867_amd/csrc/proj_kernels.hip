@@ -14,10 +14,10 @@
 //    entered only by values at or above the list's K-th value.
 // Every holder of a batch row in a workgroup (two lane halves in each
 // wavefront along the vocabulary) writes its pair and list as a partial;
-// the split top-k merge kernel combines a row's partials (Eq. 4 for the
+// a second kernel (topk_merge_held) combines a row's partials (Eq. 4 for the
 // pairs, the key order for the lists).
 #include "proj.hpp"
-#include "topk.hpp"
+#include "topk_held.hpp"
 
 namespace osm {
 
@@ -464,11 +464,7 @@ hipError_t launch_proj_topk(const void* h, const void* w, float* vals, int32_t* 
         launch_part<PjFusedN, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    constexpr int WB = TK_BLOCK / 64;
-    dim3 mgrid((unsigned)((N + WB - 1) / WB));
-    hipLaunchKernelGGL((topk_merge<TK_ONLINE>), mgrid, dim3(TK_BLOCK), 0, st, pkeys, pmd, vals,
-                       idx, N, Sp, K);
-    return hipGetLastError();
+    return launch_merge_held<TK_ONLINE>(pkeys, pmd, vals, idx, N, Sp, K, st);
 }
 
 }  // namespace osm

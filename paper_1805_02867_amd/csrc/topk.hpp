@@ -423,7 +423,7 @@ __device__ __forceinline__ float sum_exp_fixed(float d, const float (&x)[N], flo
 // c.  With segs = 1 a virtual row is a row.  PART = false writes the final
 // outputs (segs must be 1); PART = true writes, per virtual row, its K
 // largest keys (indices relative to the start of the row; 0 = fewer than K)
-// and its normalizer pair, which topk_merge combines.
+// and its normalizer pair, which held_merge (topk_held.hpp) combines.
 // LDS slots of one wavefront's list + queue region for a shape: keys are
 // queued by the offer of a batch of candidate vectors (at most 64 E keys) or
 // of one scalar element per lane, each followed by a check of the selection
@@ -454,10 +454,10 @@ struct TopkSmem {
 // largest keys and pair go to pkeys[vr * K ...] and pmd[vr].  The caller has
 // emptied the group's lists and thresholds (and, for W > 1, synchronised).
 // Returns whether this wavefront holds the row's result (all of them for
-// W = 1, the row's first for W > 1).  COH: the partial is stored with
+// W = 1, the row's first for W > 1).  PART: the partial is stored with
 // agent-scope atomic stores, which reach the device's coherence point
 // without cache maintenance, for another workgroup of the same kernel.
-template <typename T, int W, int U, int VAR, bool PART, bool COH = false>
+template <typename T, int W, int U, int VAR, bool PART>
 __device__ __forceinline__ bool topk_vrow(TopkSmem<T, U>& sm, const T* __restrict__ x,
                                           float* __restrict__ vals, int32_t* __restrict__ idx,
                                           uint64_t* __restrict__ pkeys, MD* __restrict__ pmd,
@@ -800,18 +800,13 @@ __device__ __forceinline__ bool topk_vrow(TopkSmem<T, U>& sm, const T* __restric
         }
     }
     if constexpr (PART) {
-        if constexpr (COH) {
-            if (lane < K)
-                __hip_atomic_store(pkeys + vr * K + lane, key, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            if (VAR != TK_VALUES && lane == 0)
-                __hip_atomic_store(reinterpret_cast<uint64_t*>(pmd + vr),
-                                   __builtin_bit_cast(uint64_t, md), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            if (lane < K) pkeys[vr * K + lane] = key;
-            if (VAR != TK_VALUES && lane == 0) pmd[vr] = md;
-        }
+        if (lane < K)
+            __hip_atomic_store(pkeys + vr * K + lane, key, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        if (VAR != TK_VALUES && lane == 0)
+            __hip_atomic_store(reinterpret_cast<uint64_t*>(pmd + vr),
+                               __builtin_bit_cast(uint64_t, md), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     } else if (lane < K) {
         if constexpr (VAR == TK_VALUES) {
             vals[row * K + lane] = key_value(key);
@@ -824,161 +819,21 @@ __device__ __forceinline__ bool topk_vrow(TopkSmem<T, U>& sm, const T* __restric
     return true;
 }
 
-template <typename T, int W, int U, int VAR, bool PART>
+template <typename T, int W, int U, int VAR>
 __global__ __launch_bounds__(TK_BLOCK) void topk_fused(const T* __restrict__ x,
                                                       float* __restrict__ vals,
-                                                      int32_t* __restrict__ idx,
-                                                      uint64_t* __restrict__ pkeys,
-                                                      MD* __restrict__ pmd, int64_t N, int64_t V,
-                                                      int K, int64_t seg, int64_t segs) {
+                                                      int32_t* __restrict__ idx, int64_t N,
+                                                      int64_t V, int K) {
     constexpr int RB = TK_BLOCK / 64 / W;   // rows per workgroup
     __shared__ TopkSmem<T, U> sm;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t vr = (int64_t)blockIdx.x * RB + wv / W;
-    const bool live = vr < N * segs;        // uniform per wavefront (and per row)
+    const bool live = vr < N;               // uniform per wavefront (and per row)
     if (lane < K) sm.region[wv][lane] = 0;  // empty list
     if (lane == 0) sm.published[wv] = 0;
     if constexpr (W > 1) __syncthreads();
     if (!live) return;                      // whole rows leave together
-    topk_vrow<T, W, U, VAR, PART>(sm, x, vals, idx, pkeys, pmd, V, K, seg, segs, vr);
-}
-
-// Second stage of the split top-k: per row, the K largest of the S * K
-// chunk keys (filtered against the running threshold as in the one-pass
-// kernel) and the fixed-order merge (Eq. 4) of the S chunk pairs.  One
-// wavefront per row.
-constexpr int TK_MERGE_B = 8;  // keys per lane in flight
-
-// One row by one wavefront: region holds at least region_slots(64) slots,
-// its first K already empty; B keys per lane are in flight, and the
-// selection trigger is checked after every 64 appended keys.  The pairs'
-// loads are issued with the first keys', so that a row of up to 64 B keys and
-// 64 chunks costs one round trip.  COH: the partials are read with
-// agent-scope atomic loads (written by other workgroups of the same kernel).
-template <int VAR, bool COH = false, int B = TK_MERGE_B>
-__device__ __forceinline__ void topk_merge_row(uint64_t* region, const uint64_t* pkeys,
-                                               const MD* pmd, float* __restrict__ vals,
-                                               int32_t* __restrict__ idx, int64_t row, int64_t S,
-                                               int K) {
-    const int lane = threadIdx.x & 63;
-    TopkWave<1> tw{region, nullptr, 0, K, 0, 0ull, -__builtin_inff(), 0ull};
-    const int fa = flush_at(K);
-    const int64_t n = S * K;
-    const uint64_t* pk = pkeys + row * n;
-    const MD* pm = pmd + row * S;
-    auto load_md = [&](int64_t j) {
-        if constexpr (COH)
-            return __builtin_bit_cast(MD, __hip_atomic_load(reinterpret_cast<const uint64_t*>(pm + j),
-                                                            __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT));
-        else
-            return pm[j];
-    };
-    // the first pair of this lane (chunk `lane`), requested before the keys
-    MD md = md_empty();
-    if constexpr (VAR != TK_VALUES) {
-        if (lane < S) md = load_md(lane);
-    }
-    auto load_keys = [&](uint64_t (&k)[B], int64_t c) {
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const int64_t j = c + b * 64 + lane;
-            if constexpr (COH)
-                k[b] = j < n ? __hip_atomic_load(pk + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                             : 0ull;
-            else
-                k[b] = j < n ? pk[j] : 0ull;
-        }
-    };
-    uint64_t key;
-    if (n <= 64 * B && K <= TK_ROUNDS_MAX) {
-        // every key in registers at once: K rounds of the wavefront maximum
-        // below the last key taken (0 marks a missing key and is never taken)
-        uint64_t k[B];
-        load_keys(k, 0);
-        int found;
-        key = select_topk<B>(k, B, K, &found);
-    } else {
-        for (int64_t c = 0; c < n; c += 64 * B) {
-            uint64_t k[B];
-            load_keys(k, c);
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                tw.append(k[b] > tw.tau, k[b]);  // 0 never passes
-                if (tw.qcount >= fa) tw.flush();
-            }
-        }
-        tw.flush();
-        key = tw.mine;
-    }
-    if constexpr (VAR != TK_VALUES) {
-        // chunks lane, lane + 64, ... in order, then the butterfly
-        for (int64_t j = lane + 64; j < S; j += 64) md = md_merge(md, load_md(j));
-        md = group_merge<64>(md);  // every lane takes part
-    }
-    if (lane < K) {
-        if constexpr (VAR == TK_VALUES) {
-            vals[row * K + lane] = key_value(key);
-        } else {
-            const float Sv = md.s, rd = 1.0f / md.d;
-            vals[row * K + lane] = out_elem(key_value(key), Sv, rd);
-        }
-        idx[row * K + lane] = key_index(key);
-    }
-}
-
-template <int VAR>
-__global__ __launch_bounds__(TK_BLOCK) void topk_merge(const uint64_t* __restrict__ pkeys,
-                                                      const MD* __restrict__ pmd,
-                                                      float* __restrict__ vals,
-                                                      int32_t* __restrict__ idx, int64_t N,
-                                                      int64_t S, int K) {
-    constexpr int WB = TK_BLOCK / 64;
-    constexpr int REGION = region_slots(64);
-    __shared__ uint64_t region[WB][REGION];
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row = (int64_t)blockIdx.x * WB + wv;
-    if (lane < K) region[wv][lane] = 0;
-    if (row >= N) return;
-    topk_merge_row<VAR>(region[wv], pkeys, pmd, vals, idx, row, S, K);
-}
-
-// Split top-k in one kernel: chunk c of row r is workgroup r * segs + c (four
-// wavefronts), which leaves its partial (K keys, pair) at the coherence
-// point; the workgroup that completes a row (ctr[r] counts its chunks) merges
-// the row's partials there and then, instead of a second kernel.  ctr starts
-// at zero and is left at zero (the merger resets its row's count).
-template <typename T, int U, int VAR>
-__global__ __launch_bounds__(TK_BLOCK) void topk_split1(const T* __restrict__ x,
-                                                       float* __restrict__ vals,
-                                                       int32_t* __restrict__ idx,
-                                                       uint64_t* __restrict__ pkeys,
-                                                       MD* __restrict__ pmd, uint32_t* ctr,
-                                                       int64_t N, int64_t V, int K, int64_t seg,
-                                                       int64_t segs) {
-    static_assert(topk_region<T, U>() >= region_slots(64), "the merge appends 64 keys per check");
-    __shared__ TopkSmem<T, U> sm;
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t vr = blockIdx.x;
-    if (lane < K) sm.region[wv][lane] = 0;
-    if (lane == 0) sm.published[wv] = 0;
-    __syncthreads();
-    if (!topk_vrow<T, 4, U, VAR, true, true>(sm, x, nullptr, nullptr, pkeys, pmd, V, K, seg, segs,
-                                             vr))
-        return;
-    // the partial's coherent stores have completed before the row's count moves
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const int64_t row = vr / segs;
-    uint32_t done = 0;
-    if (lane == 0)
-        done = __hip_atomic_fetch_add(ctr + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    done = __builtin_amdgcn_readfirstlane(done);
-    if (done != (uint32_t)segs - 1) return;
-    // every chunk of the row is in: its partials are read at the coherence
-    // point, after the count that says so
-    if (lane < K) sm.region[wv][lane] = 0;
-    topk_merge_row<VAR, true>(sm.region[wv], pkeys, pmd, vals, idx, row, segs, K);
-    if (lane == 0) __hip_atomic_store(ctr + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    topk_vrow<T, W, U, VAR, false>(sm, x, vals, idx, nullptr, nullptr, V, K, V, 1, vr);
 }
 
 // 16-byte vectors per lane per step, by shape and element type: enough

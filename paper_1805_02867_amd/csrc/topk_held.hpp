@@ -244,10 +244,12 @@ __device__ __forceinline__ uint32_t team_bound(Smem& sm, uint32_t m, int K) {
     return kth_bound<G, GRAN>(g, wave_hi(g), K);
 }
 
+constexpr int TK_MERGE_B = 8;  // keys per lane in one batch of a wavefront's merge
+
 // Merge of a row's n partial keys and P partial pairs by a team of W
 // wavefronts, R keys a lane at a time.  COH: the partials were written by other
-// workgroups of the same kernel.  The team's first wavefront returns true with
-// lane k's k-th key; the LDS is free on entry, and with W > 1 the workgroup's
+// workgroups of the same kernel; slot: the wavefront's list.  The team's first
+// wavefront returns true with lane k's k-th key; the LDS is free on entry, and with W > 1 the workgroup's
 // wavefronts enter together.
 template <int VAR, int W, int R, uint32_t GRAN, bool COH, class Smem>
 __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* pk, const MD* pm,
@@ -267,12 +269,18 @@ __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* p
         if (tr < P) a = load_md(tr);
     }
     HeldList hl{sm.list[slot], K, 0, 0ull};
+    uint64_t top = 0;  // W = 1, K = 1: the largest key, without threshold or list
 #pragma unroll 1
     for (int64_t b = 0; b < n; b += TR * R) {
         uint64_t k[R];
         const int64_t left = n - b;
 #pragma unroll
         for (int i = 0; i < R; ++i) k[i] = tr + i * TR < left ? load(pk + b + tr + i * TR) : 0ull;
+        if (W == 1 && K == 1) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) top = k[i] > top ? k[i] : top;
+            continue;
+        }
         uint32_t t = 0;
         if (b > 0) {
             // the list's K-th key filters the later batches
@@ -316,7 +324,8 @@ __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* p
     }
     if constexpr (W == 1) {
         wave_sync();
-        *key = held_finish<1>(&sm.list[slot], &hl.n, K);
+        if (K == 1) *key = wave_max_key(top);
+        else *key = held_finish<1>(&sm.list[slot], &hl.n, K);
         *md = a;
         return true;
     } else {
@@ -610,7 +619,7 @@ __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_held(
 }
 
 // Second stage of a two-kernel split: a row's n = S K partial keys and S pairs
-// by W wavefronts (W = 1: four rows per workgroup), n <= 64 W R.
+// by W wavefronts (W = 1: four rows per workgroup), R keys a lane at a time.
 template <int VAR, int W, int R>
 __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_merge_held(
     const uint64_t* __restrict__ pkeys, const MD* __restrict__ pmd, float* __restrict__ vals,
@@ -621,13 +630,38 @@ __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_merge_held(
     if (W == 1 && row >= N) return;
     uint64_t key;
     MD md;
-    if (held_merge<VAR, W, R, 1, false>(sm, W == 1 ? wv : 0, pkeys + row * S * K, pmd + row * S, S * K,
+    if (held_merge<VAR, W, R, 1, false>(sm, wv, pkeys + row * S * K, pmd + row * S, S * K,
                                      S, K, &key, &md))
         held_store<VAR>(key, md, vals, idx, row, K);
 }
 
 // ------------------------------------------------------------------ launchers
 constexpr int TH_RMAX = 16;  // vectors per lane
+
+// A wavefront per row while it holds the row's keys in one batch (512), then a
+// workgroup of four or sixteen: the merge of 2004 pairs and 10020 keys for each
+// of 64 rows took ~40 us with a wavefront per row, in twenty batches on a
+// quarter of the CUs (the whole projection + top-5 at 64 x 4096 x 128256: 216
+// -> 191 us; 37 x 512 x 50001 top-16: 77.5 -> 50.7).
+template <int VAR>
+hipError_t launch_merge_held(const uint64_t* pkeys, const MD* pmd, float* vals, int32_t* idx,
+                             int64_t N, int64_t S, int K, hipStream_t st) {
+    const int64_t n = S * K;
+    const dim3 rows((unsigned)N), quads((unsigned)((N + 3) / 4));
+    if (n <= 512)
+        hipLaunchKernelGGL((topk_merge_held<VAR, 1, 8>), quads, dim3(256), 0, st, pkeys, pmd, vals,
+                           idx, N, S, K);
+    else if (n <= 2048)
+        hipLaunchKernelGGL((topk_merge_held<VAR, 4, 8>), rows, dim3(256), 0, st, pkeys, pmd, vals,
+                           idx, N, S, K);
+    else if (n <= 4096)
+        hipLaunchKernelGGL((topk_merge_held<VAR, 4, 16>), rows, dim3(256), 0, st, pkeys, pmd, vals,
+                           idx, N, S, K);
+    else
+        hipLaunchKernelGGL((topk_merge_held<VAR, 16, 16>), rows, dim3(1024), 0, st, pkeys, pmd,
+                           vals, idx, N, S, K);
+    return hipGetLastError();
+}
 
 // Vectors per lane: the smallest of 1, 2, 3, 4, 6, 8, 12, 16 that holds the
 // row's `nv` vectors (a lane's spare vectors cost a masked load each).
