@@ -19,6 +19,8 @@
 // result register r < 16.
 #pragma once
 
+#include <type_traits>
+
 #include "md.hpp"
 
 namespace osm {
@@ -263,6 +265,204 @@ __device__ __forceinline__ void pj_run(const uint16_t* __restrict__ X, int64_t n
         rx = rxn;
         ry = ryn;
     }
+}
+
+// ------------------------------------------------- 256 x 256, two wave groups
+// The 256 x 256 tile by eight wavefronts in two groups that take turns: while
+// the four wavefronts of one group (one per SIMD) multiply, the other group's
+// read their fragments and issue loads, so each SIMD's matrix core always has
+// a wavefront on it.  In pj_run all eight read after each barrier together and
+// the matrix cores wait for the first fragments.  Measured: matrix cores busy
+// 77% of the cycles against 60%; logits of 4000 x 4096 x 32000 977 -> 893 us,
+// 512 x 4096 x 128256 545 -> 482 (1.12 PF/s), 4000 x 4096 x 128256 3825 -> 3490
+// (1.20 PF/s).  What bounds it now is power (the clock settles near 1.6 GHz)
+// and the loads' way into the LDS: without the loads it runs at 1.45 PF/s,
+// without any wait for them no faster than with.
+//
+// A K step of 64 is four phases, one per quadrant of a wavefront's block.
+// Wavefront (wx, wy) multiplies, with each half h of the X tile (128 rows) and
+// half g of the Y tile, the 64 rows 128 h + 64 wx + ... by the 32 columns
+// 128 g + 32 wy + ..., so every wavefront reads all four half tiles, one per
+// phase, and a half tile is free for its next load as soon as its phase is
+// over:
+//   phase 1 reads X half 0, multiplies with the Y half 0 already in registers;
+//   phase 2 reads Y half 1, multiplies X half 0 with it;
+//   phase 3 reads X half 1, multiplies it with Y half 1;
+//   phase 4 reads the next step's Y half 0, multiplies X half 1 with Y half 0.
+// A phase is a read section and a multiply section with a barrier after each;
+// group 1 runs one section behind group 0 (an extra barrier at the start of a
+// tile, one of group 0 at its end).  A read section ends with its reads done.
+// The multiply section of a phase also issues the load, for the K step after
+// next, of the half tile that the phase before read: group 1 read it two
+// sections ago, or three, so a load never meets a read.  (Issued in the read
+// sections, the loads cost 2-3% more.)
+//
+// Counting.  Every multiply section issues two loads a thread.  What section j
+// loads is first read in section j + 7, by group 0 one barrier after group 1's
+// read section j + 6 ends: so every read section waits until at most 10 loads
+// (those of the last five multiply sections) are in flight.  Loads past the
+// last step read beyond the descriptor (zeros), which keeps the counts uniform.
+template <class C>
+struct PpSmem {
+    uint16_t x[2][C::TX][PJ_BK];  // [stage]
+    uint16_t y[2][C::TY][PJ_BK];
+};
+
+// Row of the block's 32 x 32 blocks: X rows of block mi, Y columns of block ni
+// (offsets within the tile, before the lane's own part).
+__device__ __forceinline__ int pp_row(int wx, int mi) {
+    return (mi >> 1) * 128 + wx * 64 + (mi & 1) * 32;
+}
+__device__ __forceinline__ int pp_col(int wy, int ni) { return ni * 128 + wy * 32; }
+
+__device__ __forceinline__ void pp_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The workgroup's tiles t0 <= t < t1 as pj_run, for the 256 x 256 tile in 2 x 4
+// wavefronts: epi(t, x0, y0, acc) with acc[mi][ni] the block at pp_row(wx, mi),
+// pp_col(wy, ni).  The stages stay in use while epi runs, and nothing else may
+// wait on vmcnt order: epi's own loads and stores only make later waits longer.
+template <class C, class Coords, class Epi>
+__device__ __forceinline__ void pp_run(const uint16_t* __restrict__ X, int64_t nx,
+                                       const uint16_t* __restrict__ Y, int64_t ny, int64_t K,
+                                       int64_t t0, int64_t t1, PpSmem<C>& sm, Coords&& coords,
+                                       Epi&& epi) {
+    static_assert(C::TX == 256 && C::TY == 256 && C::WX == 2 && C::WY == 4, "four half tiles");
+    constexpr int KS = PJ_BK / 16;
+    constexpr int STAGE = 256 * PJ_BK * 2, HALF = 128 * PJ_BK * 2;  // bytes
+    const int wave = pj_wave(), wx = wave >> 2, wy = wave & 3;
+    const int lane = threadIdx.x & 63;
+    // A fragment of sub-step ks is at off ^ 32 ks from the block's start: the
+    // slot's XOR term is the lane's alone, and ks moves the slot's upper two
+    // bits.  Kept as one offset per operand (PjFragOff's four would not fit
+    // beside the fused kernel's lists), re-derived at each read section.
+    uint32_t xoff = PjFragOff<1>::make(wx * 64).off[0], yoff = PjFragOff<1>::make(wy * 32).off[0];
+    const char* const xb = reinterpret_cast<const char*>(&sm.x[0][0][0]);
+    const char* const yb = reinterpret_cast<const char*>(&sm.y[0][0][0]);
+    auto frag = [](const char* b, uint32_t off, int at) {
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(b + off + at));
+    };
+    // load j of a half tile: rows 64 j + 8 wave + lane / 8 of it
+    const int lrow = 8 * wave + (lane >> 3), kc = pj_slot(lrow, lane & 7);
+    uint32_t voff = (uint32_t)(lrow * K * 2 + kc * 16);
+    const uint32_t vstep = (uint32_t)(64 * K * 2);
+    auto load = [&](uint16_t (&tile)[256][PJ_BK], int half, __amdgpu_buffer_rsrc_t rs, int64_t k,
+                    int j) {
+        const int k0 = (int)(k * PJ_BK);
+        const bool oob = k0 + kc * 8 >= (int)K;  // past the end of the rows
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rs,
+            (__attribute__((address_space(3))) void*)(&tile[half * 128][0] +
+                                                      64 * (8 * j + wave) * 8),
+            16, oob ? PJ_OOB : voff + (2 * half + j) * vstep, k0 * 2, 0, 0);
+    };
+    const int64_t nk = pj_steps(K);
+    int64_t x0, y0;
+    coords(t0, x0, y0);
+    __amdgpu_buffer_rsrc_t rx = pj_rsrc(X, nx, K, x0), ry = pj_rsrc(Y, ny, K, y0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            load(sm.y[s], h, ry, s, 0);
+            load(sm.y[s], h, ry, s, 1);
+            load(sm.x[s], h, rx, s, 0);
+            load(sm.x[s], h, rx, s, 1);
+        }
+    bf16x8 a[2][KS], b[2][KS];  // X half (two blocks), Y halves
+    asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    pp_barrier();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) b[0][ks] = frag(yb, yoff ^ (32 * ks), 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    pp_barrier();
+
+    for (int64_t t = t0; t < t1; ++t) {
+        int64_t xn = x0, yn = y0;
+        const bool more = t + 1 < t1;
+        if (more) coords(t + 1, xn, yn);
+        // past the last tile: descriptors that hold nothing
+        const __amdgpu_buffer_rsrc_t rxn = pj_rsrc(X, more ? nx : xn, K, xn),
+                                     ryn = pj_rsrc(Y, more ? ny : yn, K, yn);
+        f32x16 acc[C::MI][C::NI];
+#pragma unroll
+        for (int mi = 0; mi < C::MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < C::NI; ++ni)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.0f;
+        auto read_x = [&](int stage, int h) {
+            asm volatile("" : "+v"(xoff));
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi)
+                    a[mi][ks] = frag(xb, xoff ^ (32 * ks),
+                                     stage * STAGE + h * HALF + mi * 32 * PJ_BK * 2);
+        };
+        auto read_y = [&](int stage, int g, bf16x8 (&to)[KS]) {
+            asm volatile("" : "+v"(yoff));
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                to[ks] = frag(yb, yoff ^ (32 * ks), stage * STAGE + g * HALF);
+        };
+        auto end_read = [&]() {
+            asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)" ::: "memory");
+            pp_barrier();
+        };
+        auto multiply = [&](int h, int g, const bf16x8 (&bb)[KS], auto&& issue) {
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi) {
+                    acc[2 * h + mi][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        a[mi][ks], bb[ks], acc[2 * h + mi][g], 0, 0, 0);
+                    if (mi == 0 && (ks == 0 || ks == 2)) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        issue(ks / 2);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            __builtin_amdgcn_s_setprio(0);
+            pp_barrier();
+        };
+        // K step k in stage s, whose Y half 0 is in p; q is free.
+        auto step = [&](int64_t k, auto s_, bf16x8 (&p)[KS], bf16x8 (&q)[KS]) {
+            constexpr int s = decltype(s_)::value;
+            const bool next = k + 2 >= nk;  // the loads belong to the next tile
+            const int64_t lk = next ? k + 2 - nk : k + 2;
+            const __amdgpu_buffer_rsrc_t lx = next ? rxn : rx, ly = next ? ryn : ry;
+            read_x(s, 0);
+            end_read();
+            multiply(0, 0, p, [&](int j) { load(sm.y[s], 0, ly, lk, j); });
+            read_y(s, 1, q);
+            end_read();
+            multiply(0, 1, q, [&](int j) { load(sm.x[s], 0, lx, lk, j); });
+            read_x(s, 1);
+            end_read();
+            multiply(1, 1, q, [&](int j) { load(sm.y[s], 1, ly, lk, j); });
+            read_y(s ^ 1, 0, q);
+            end_read();
+            multiply(1, 0, p, [&](int j) { load(sm.x[s], 1, lx, lk, j); });
+        };
+        if (wx == 1) pp_barrier();
+        for (int64_t k = 0; k < nk; k += 2) {
+            step(k, std::integral_constant<int, 0>{}, b[0], b[1]);
+            step(k + 1, std::integral_constant<int, 1>{}, b[1], b[0]);
+        }
+        if (wx == 0) pp_barrier();
+        epi(t, x0, y0, acc);
+        x0 = xn;
+        y0 = yn;
+        rx = rxn;
+        ry = ryn;
+    }
+    // the last loads (of nothing) have landed before the LDS is given back
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 }  // namespace osm

@@ -55,22 +55,45 @@ static int fused_cfg(int64_t N, int K) {
 // logical ids covers a compact block of tiles.
 constexpr int64_t PJ_GROUP = 8;
 
+// This workgroup's tile in that order; false if it has none.
+template <class C>
+__device__ __forceinline__ bool logits_tile(int64_t N, int64_t V, int64_t per, int64_t& x0,
+                                            int64_t& y0) {
+    const int64_t nb = (N + C::TX - 1) / C::TX, nt = (V + C::TY - 1) / C::TY;
+    const int64_t lid = xcd_logical(blockIdx.x, per);
+    if (lid >= nb * nt) return false;
+    const int64_t in_group = PJ_GROUP * nt;
+    const int64_t first = (lid / in_group) * PJ_GROUP;
+    const int64_t gsize = nb - first < PJ_GROUP ? nb - first : PJ_GROUP;
+    x0 = (first + (lid % in_group) % gsize) * C::TX;  // batch
+    y0 = ((lid % in_group) / gsize) * C::TY;          // vocabulary
+    return true;
+}
+
+// One 32 x 32 block of logits, whose first row and column are given.
+// Streaming stores: the logits are not read again by this kernel (measured
+// 11-12% faster at 4000 x 1024 x 32000, also for a top-k reading them next;
+// neutral at H = 4096).
+__device__ __forceinline__ void store_block(const f32x16& acc, float* __restrict__ out, int64_t N,
+                                            int64_t V, int64_t row0, int64_t col0) {
+    const int lane = threadIdx.x & 63;
+    const int64_t col = col0 + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int64_t row = row0 + row_in_32(i, lane);
+        if (row < N && col < V) __builtin_nontemporal_store(acc[i], out + row * V + col);
+    }
+}
+
 template <class C>
 __global__ __launch_bounds__(C::NT) void proj_logits(const uint16_t* __restrict__ h,
                                                      const uint16_t* __restrict__ w,
                                                      float* __restrict__ out, int64_t N,
                                                      int64_t H, int64_t V, int64_t per) {
     __shared__ typename C::Smem sm;
-    const int64_t nb = (N + C::TX - 1) / C::TX, nt = (V + C::TY - 1) / C::TY;
-    const int64_t lid = xcd_logical(blockIdx.x, per);
-    if (lid >= nb * nt) return;  // the whole workgroup leaves
-    const int64_t in_group = PJ_GROUP * nt;
-    const int64_t first = (lid / in_group) * PJ_GROUP;
-    const int64_t gsize = nb - first < PJ_GROUP ? nb - first : PJ_GROUP;
-    const int64_t bx0 = (first + (lid % in_group) % gsize) * C::TX;  // batch
-    const int64_t vy0 = ((lid % in_group) / gsize) * C::TY;          // vocabulary
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wx = wave / C::WY, wy = wave % C::WY;
+    int64_t bx0, vy0;
+    if (!logits_tile<C>(N, V, per, bx0, vy0)) return;  // the whole workgroup leaves
+    const int wave = threadIdx.x >> 6, wx = wave / C::WY, wy = wave % C::WY;
     pj_run<C>(
         h, N, w, V, H, 0, 1, sm,
         [&](int64_t, int64_t& x0, int64_t& y0) {
@@ -78,20 +101,36 @@ __global__ __launch_bounds__(C::NT) void proj_logits(const uint16_t* __restrict_
             y0 = vy0;
         },
         [&](int64_t, int64_t x0, int64_t y0, f32x16 (&acc)[C::MI][C::NI]) {
-            // streaming stores: the logits are not read again by this kernel
-            // (measured 11-12% faster at 4000 x 1024 x 32000, also for a top-k
-            // reading them next; neutral at H = 4096)
 #pragma unroll
             for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
                 for (int ni = 0; ni < C::NI; ++ni)
+                    store_block(acc[mi][ni], out, N, V, x0 + wx * 32 * C::MI + mi * 32,
+                                y0 + wy * 32 * C::NI + ni * 32);
+        });
+}
+
+template <class C>
+__global__ __launch_bounds__(C::NT) void proj_logits_pp(const uint16_t* __restrict__ h,
+                                                        const uint16_t* __restrict__ w,
+                                                        float* __restrict__ out, int64_t N,
+                                                        int64_t H, int64_t V, int64_t per) {
+    __shared__ PpSmem<C> sm;
+    int64_t bx0, vy0;
+    if (!logits_tile<C>(N, V, per, bx0, vy0)) return;  // the whole workgroup leaves
+    const int wave = pj_wave(), wx = wave / C::WY, wy = wave % C::WY;
+    pp_run<C>(
+        h, N, w, V, H, 0, 1, sm,
+        [&](int64_t, int64_t& x0, int64_t& y0) {
+            x0 = bx0;
+            y0 = vy0;
+        },
+        [&](int64_t, int64_t x0, int64_t y0, f32x16 (&acc)[C::MI][C::NI]) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int64_t row = x0 + wx * 32 * C::MI + mi * 32 + row_in_32(i, lane);
-                        const int64_t col = y0 + wy * 32 * C::NI + ni * 32 + (lane & 31);
-                        if (row < N && col < V)
-                            __builtin_nontemporal_store(acc[mi][ni][i], out + row * V + col);
-                    }
+            for (int mi = 0; mi < C::MI; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < C::NI; ++ni)
+                    store_block(acc[mi][ni], out, N, V, x0 + pp_row(wx, mi), y0 + pp_col(wy, ni));
         });
 }
 
@@ -387,21 +426,25 @@ __global__ __launch_bounds__(C::NT) void proj_topk_part(
 }
 
 // ---------------------------------------------------------------- launchers
-template <class C>
+template <class C, bool PP>
 static hipError_t launch_logits_t(const void* h, const void* w, float* out, int64_t N, int64_t H,
                                   int64_t V, hipStream_t st) {
     const int64_t total = ((N + C::TX - 1) / C::TX) * ((V + C::TY - 1) / C::TY);
     const int64_t per = (total + 7) / 8;
-    hipLaunchKernelGGL((proj_logits<C>), dim3((unsigned)(8 * per)), dim3(C::NT), 0, st,
-                       (const uint16_t*)h, (const uint16_t*)w, out, N, H, V, per);
+    if constexpr (PP)
+        hipLaunchKernelGGL((proj_logits_pp<C>), dim3((unsigned)(8 * per)), dim3(C::NT), 0, st,
+                           (const uint16_t*)h, (const uint16_t*)w, out, N, H, V, per);
+    else
+        hipLaunchKernelGGL((proj_logits<C>), dim3((unsigned)(8 * per)), dim3(C::NT), 0, st,
+                           (const uint16_t*)h, (const uint16_t*)w, out, N, H, V, per);
     return hipGetLastError();
 }
 
 hipError_t launch_proj_logits(const void* h, const void* w, float* out, int64_t N, int64_t H,
                               int64_t V, int cus, hipStream_t st) {
     const int64_t big = ((N + PjBig::TX - 1) / PjBig::TX) * ((V + PjBig::TY - 1) / PjBig::TY);
-    if (big >= 2 * (int64_t)cus) return launch_logits_t<PjBig>(h, w, out, N, H, V, st);
-    return launch_logits_t<PjSmall>(h, w, out, N, H, V, st);
+    if (big >= 2 * (int64_t)cus) return launch_logits_t<PjBig, true>(h, w, out, N, H, V, st);
+    return launch_logits_t<PjSmall, false>(h, w, out, N, H, V, st);
 }
 
 void proj_topk_shape(int64_t N, int64_t V, int K, int cus, int64_t* S, int64_t* tiles,

@@ -1,0 +1,76 @@
+"""The 256 x 256 projection core (calls of 512 tiles and more, and the fused
+top-k past 128 rows) at the edges of its K steps and tiles, and the fused
+epilogue on logits in rising and falling order and all equal.  Every product
+and sum is exact in binary32 whatever its order, so logits must equal the
+binary64 ones bit for bit and top-k indices the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1805_02867_amd as osm
+from parity import rel_err_f32, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need an MI355X; none is visible")
+    return torch.device("cuda:0")
+
+
+def exact_inputs(N, H, V, seed, dev):
+    """Small integers times powers of two: |logit| < 2^6, in steps of 2^-7."""
+    g = torch.Generator(device=dev).manual_seed(seed)
+    h = torch.randint(-4, 5, (N, H), generator=g, device=dev).to(torch.bfloat16) * 0.125
+    w = torch.randint(-4, 5, (V, H), generator=g, device=dev).to(torch.bfloat16) * 0.0625
+    return h, w
+
+
+def logits64(h, w):
+    return torch.matmul(h.double(), w.double().t())
+
+
+def check_topk(h, w, K, what):
+    print(what, flush=True)
+    vals, idx = osm.proj_softmax_topk(h, w, K)
+    torch.cuda.synchronize()
+    v64, z64 = oracle.topk(to_host(logits64(h, w)), K, "f64")
+    assert np.array_equal(to_host(idx), z64), what
+    assert (rel_err_f32(to_host(vals), v64) <= 1).all(), what
+
+
+@pytest.mark.parametrize("H", [8, 64, 72, 128, 136, 192, 1032])
+def test_logits_k_step_edges(dev, H):
+    N, V = 4097, 8001  # 17 x 32 tiles, one row and 65 columns into the last
+    h, w = exact_inputs(N, H, V, seed=H, dev=dev)
+    out = torch.full((N, V), 7.0, device=dev)
+    print(f"logits H={H}", flush=True)
+    osm.proj(h, w, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out.double(), logits64(h, w))
+
+
+@pytest.mark.parametrize("H", [8, 64, 136, 256])
+@pytest.mark.parametrize("K", [1, 5, 8, 9, 16])
+def test_topk_tile_edges(dev, H, K):
+    for N, V in ((129, 257), (256, 2560), (257, 5121), (513, 33), (1025, 700)):
+        check_topk(*exact_inputs(N, H, V, seed=N + V + H + K, dev=dev), min(K, V),
+                   f"fused N={N} H={H} V={V} K={K}")
+
+
+@pytest.mark.parametrize("N", [40, 100, 200, 1100])
+@pytest.mark.parametrize("K", [1, 5, 8, 16])
+def test_topk_of_ordered_logits(dev, N, K):
+    """Rising logits make every entry a new maximum, equal ones are all ties."""
+    V, H = 9000, 64
+    h = torch.zeros((N, H), dtype=torch.bfloat16, device=dev)
+    h[:, 0], h[:, 1] = 1.0, 1.0 / 128
+    v = torch.arange(V, device=dev)
+    for what, order in (("rising", v), ("falling", V - 1 - v), ("equal", v * 0)):
+        w = torch.zeros((V, H), dtype=torch.bfloat16, device=dev)
+        w[:, 0] = torch.div(order, 128, rounding_mode="floor").to(torch.bfloat16)
+        w[:, 1] = (order % 128).to(torch.bfloat16)
+        check_topk(h, w, K, f"{what} N={N} K={K}")
