@@ -28,10 +28,12 @@ using PjBig = PjCfg<256, 256, 2, 4>;
 using PjSmall = PjCfg<128, 128, 2, 2>;
 // Fused, by batch size and K (the vocabulary tile is 256 entries in all; the
 // lanes' top-K lists live in registers):
-//  * 256 x 256 (K <= 8, N > 128): 2 x 4 wavefronts, two batch rows per lane;
-//    128 result registers and at most 128 others per lane, so two
-//    wavefronts share each SIMD and one's epilogue overlaps the other's
-//    products;
+//  * 256 x 256 (K <= 8, N > 128): the two-group core's 2 x 4 wavefronts, two
+//    batch rows per lane; 128 result registers and 128 others per lane (the
+//    lists and the row state are stored away once per tile, around the K
+//    loop), so two wavefronts share each SIMD.  Projection + top-5, us, against
+//    the same epilogue's forerunner on pj_run: 4000 x 4096 x 32000 950 -> 875,
+//    4000 x 1024 x 32000 384 -> 307, 512 x 4096 x 128256 566 -> 494;
 //  * 256 x 128 in 2 x 4 wavefronts (8 < K <= 16, N > 1024): one batch row per
 //    lane, also two wavefronts per SIMD;
 //  * 256 x 128 in 1 x 4 wavefronts (otherwise, N > 64): one batch row per
@@ -137,31 +139,6 @@ __global__ __launch_bounds__(C::NT) void proj_logits_pp(const uint16_t* __restri
 // ------------------------------------------------------------ fused top-k
 constexpr int64_t PJ_CB = 4, PJ_SB = 8;  // block of chunks x batch strips per XCD
 
-// Insert `key` into a lane's list (descending, K valid entries in a
-// register array of KC, unused entries 0); the caller has checked that key
-// exceeds the K-th entry.  Every entry moves at most one place, computed
-// from the old list, so all positions update at once.
-template <int KC>
-__device__ __forceinline__ void list_insert(uint64_t (&L)[KC], int K, uint64_t key) {
-    uint64_t prev = L[0];
-    L[0] = key > L[0] ? key : L[0];
-#pragma unroll
-    for (int i = 1; i < KC; ++i) {
-        const uint64_t cur = L[i];
-        const uint64_t moved = key > prev ? prev : (key > cur ? key : cur);
-        L[i] = i < K ? moved : cur;
-        prev = cur;
-    }
-}
-
-template <int KC>
-__device__ __forceinline__ uint64_t list_kth(const uint64_t (&L)[KC], int K) {
-    uint64_t t = 0;
-#pragma unroll
-    for (int i = 0; i < KC; ++i) t = (i == K - 1) ? L[i] : t;
-    return t;
-}
-
 // A copy of an accumulator register made where it is used.  Left to itself
 // the compiler moves every accumulator of the tile into vector registers at
 // once when the products end (they are read by vector instructions from
@@ -173,29 +150,70 @@ __device__ __forceinline__ float acc_reread(float a) {
     return r;
 }
 
-// Bit j of a candidate mask for entry x against threshold t, set when x is
-// below t: the sign of x - t, moved to bit j in vector registers (a compare
-// would give a wave-wide scalar mask per entry, and the compiler keeps many
-// of those alive at once).  x == t gives +0, i.e. not below; a NaN
-// difference may set either value, and every candidate is checked again
-// before it is offered.
-__device__ __forceinline__ uint32_t below_bit(float x, float t, int j) {
-    return (__float_as_uint(x - t) >> 31) << j;
+// m = 2 m + (x >= t): one entry's bit of a candidate mask, by a compare and an
+// add with its result as the carry (a compare on its own would give a
+// wave-wide scalar mask per entry, to be moved into the lanes by two more
+// instructions).  The first of 32 entries ends in the highest bit.
+__device__ __forceinline__ void push_bit(uint32_t& m, float x, float t) {
+    asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc"
+        : "+v"(m)
+        : "v"(x), "v"(t)
+        : "vcc");
 }
 
-// A lane's top-K list: KC registers of descending keys, K valid, unused
-// entries 0.
+// The least value above x (x finite or -infinity).
+__device__ __forceinline__ float next_up(float x) {
+    const uint32_t u = __float_as_uint(x);
+    return __uint_as_float(x == 0.0f ? 1u : (int32_t)u >= 0 ? u + 1 : u - 1);
+}
+
+// The K largest values seen, in registers: KC descending values, of which the
+// first KC - K are +infinity, so that the last one is the K-th largest
+// (-infinity while there are fewer).  Inserting a value below it changes
+// nothing.
+template <int KC>
+struct LaneVals {
+    float v[KC];
+    __device__ __forceinline__ void init(int K) {
+#pragma unroll
+        for (int i = 0; i < KC; ++i) v[i] = i < KC - K ? __builtin_inff() : -__builtin_inff();
+    }
+    __device__ __forceinline__ float kth() const { return v[KC - 1]; }
+    __device__ __forceinline__ void insert(float x) {
+#pragma unroll
+        for (int i = KC - 1; i > 0; --i) v[i] = __builtin_amdgcn_fmed3f(v[i - 1], v[i], x);
+        v[0] = __builtin_fmaxf(v[0], x);
+    }
+};
+
+// The same with the values' indices: a lane's top-K list (Alg. 4's buffer).
+// Offered in increasing index order, so an equal value goes after those there
+// already.  Per place one compare, one median and two selects, where 64-bit
+// keys took two wide compares and eight selects: the loop over a tile's
+// candidates, most of the epilogue, went from 2.7-8.6 us a row and tile to
+// 1.6-2.6 (stamps at 4000 x 1024 x 32000, K = 5), the epilogue of a tile from
+// 8.5-21.7 us to 6.6-10.6.
 template <int KC>
 struct LaneList {
-    uint64_t L[KC];
-    __device__ __forceinline__ void init() {
+    LaneVals<KC> l;
+    uint32_t ix[KC];
+    __device__ __forceinline__ void init(int K) {
+        l.init(K);
 #pragma unroll
-        for (int i = 0; i < KC; ++i) L[i] = 0ull;
+        for (int i = 0; i < KC; ++i) ix[i] = ~0u;
     }
-    // insert (key > K-th entry); returns the new K-th entry
-    __device__ __forceinline__ uint64_t insert(int K, uint64_t key) {
-        list_insert<KC>(L, K, key);
-        return list_kth<KC>(L, K);
+    __device__ __forceinline__ void insert(float x, uint32_t id) {
+#pragma unroll
+        for (int i = KC - 1; i > 0; --i) {
+            const uint32_t moved = x > l.v[i - 1] ? ix[i - 1] : id;
+            ix[i] = x > l.v[i] ? moved : ix[i];
+        }
+        ix[0] = x > l.v[0] ? id : ix[0];
+        l.insert(x);
+    }
+    // key of place i (0 = none)
+    __device__ __forceinline__ uint64_t key(int i) const {
+        return ix[i] == ~0u ? 0ull : make_key(l.v[i], ix[i]);
     }
 };
 
@@ -203,10 +221,13 @@ struct LaneList {
 // batch strip of TY rows.  Lane l of wavefront (wx, wy) holds, for batch rows
 // 32 (NI wy + ni) + l % 32 (ni < NI) of the strip, the entries
 // vbase + 32 mi + 8 (i / 4) + i % 4 (vbase = tile start + 32 MI wx + 4 (l / 32),
-// mi < MI) in result register i of block (mi, ni).  The partial of a (row, chunk) pair
+// mi < MI) in result register i of block (mi, ni); on the two-group core the
+// blocks start at pp_row and pp_col instead.  The partial of a (row, chunk) pair
 // written by this lane is p = 2 (WX c + wx) + l / 32: 2 WX S per row, each a
 // pair and K keys (0 = none).
-template <class C, int KC>
+// PP: the two-group core (256 x 256), whose stages stay in use during the
+// epilogue, so that the epilogue's columns get the LDS that the stages leave.
+template <class C, int KC, bool PP>
 __global__ __launch_bounds__(C::NT) void proj_topk_part(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w, uint64_t* __restrict__ pkeys,
     MD* __restrict__ pmd, int64_t N, int64_t H, int64_t V, int K, int64_t S, int64_t tiles,
@@ -214,11 +235,16 @@ __global__ __launch_bounds__(C::NT) void proj_topk_part(
     constexpr int NI = C::NI;
     constexpr int E = C::MI * 16;  // entries per row per lane and tile
     // entries per pass of the LDS column: the largest power of two that fits a stage
-    constexpr int EC = sizeof(typename C::Stage) >= C::NT * 64 * sizeof(float)   ? 64
+    constexpr int EC = PP                                                        ? 16
+                       : sizeof(typename C::Stage) >= C::NT * 64 * sizeof(float) ? 64
                        : sizeof(typename C::Stage) >= C::NT * 32 * sizeof(float) ? 32
                                                                                  : 16;
-    static_assert(sizeof(typename C::Stage) >= C::NT * EC * sizeof(float), "scratch fits");
-    __shared__ typename C::Smem sm;
+    static_assert(PP || sizeof(typename C::Stage) >= C::NT * EC * sizeof(float), "scratch fits");
+    struct PpAll {
+        PpSmem<C> st;
+        float scr[EC * C::NT];
+    };
+    __shared__ std::conditional_t<PP, PpAll, typename C::Smem> sm;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wx = wave / C::WY, wy = wave % C::WY;
     // Logical ids in blocks of PJ_CB chunks x up to PJ_SB batch strips, so
@@ -236,190 +262,175 @@ __global__ __launch_bounds__(C::NT) void proj_topk_part(
     const int64_t t0 = c * tiles;
     const int64_t t1 = t0 + tiles < nt ? t0 + tiles : nt;
 
-    float sr[NI], dacc[NI], tval[NI];
-    uint64_t tkey[NI];  // K-th key of the list (0 while it has fewer)
+    float sr[NI], dacc[NI];
+    float tval[NI];  // an entry below it cannot be among the row's K largest
     LaneList<KC> list[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
         sr[ni] = kEmptyS;
         dacc[ni] = 0.0f;
         tval[ni] = -__builtin_inff();
-        tkey[ni] = 0ull;
-        list[ni].init();
+        list[ni].init(K);
     }
-    float* scr = reinterpret_cast<float*>(&sm.st[1]) + threadIdx.x;  // this thread's column
+    float* scr;  // this thread's column
+    if constexpr (PP) scr = sm.scr + threadIdx.x;
+    else scr = reinterpret_cast<float*>(&sm.st[1]) + threadIdx.x;
 
-    pj_run<C>(
-        w, V, h, N, H, t0, t1, sm,
-        [&](int64_t t, int64_t& x0, int64_t& y0) {
-            x0 = t * C::TX;
-            y0 = y0s;
-        },
-        [&](int64_t, int64_t x0, int64_t, f32x16 (&acc)[C::MI][C::NI]) {
-            constexpr int E = C::MI * 16;  // entries per row per lane
-            // groups of GS consecutive entries: 8, or fewer so that there
-            // are at least KC groups (the bootstrap below needs K of them)
-            constexpr int GS = E / KC < 8 ? E / KC : 8;
-            constexpr int NG = E / GS;
-            static_assert(GS % 2 == 0 && NG >= KC, "groups hold whole entry pairs");
-            const int64_t vbase = x0 + wx * 32 * C::MI + 4 * (lane >> 5);
-            // offset from vbase of entry j (block j / 16, register j % 16)
-            auto voff = [](int j) { return (j >> 4) * 32 + 8 * ((j & 15) >> 2) + (j & 3); };
-            // Alg. 4's insertion, for an entry already known to be >= tval[ni]
-            auto offer = [&](int ni, float xv, int j) {
-                const uint64_t key = make_key(xv, (uint32_t)(vbase + voff(j)));
-                if (key > tkey[ni]) {
-                    tkey[ni] = list[ni].insert(K, key);
-                    // until the list holds K keys the threshold stays as it is
-                    if (tkey[ni] != 0) tval[ni] = key_value(tkey[ni]);
+    auto coords = [&](int64_t t, int64_t& x0, int64_t& y0) {
+        x0 = t * C::TX;
+        y0 = y0s;
+    };
+    auto epi = [&](int64_t, int64_t x0, int64_t, f32x16 (&acc)[C::MI][C::NI]) {
+        // groups of GS consecutive entries: 8, or fewer so that there
+        // are at least KC groups (the bootstrap below needs K of them)
+        constexpr int GS = E / KC < 8 ? E / KC : 8;
+        constexpr int NG = E / GS;
+        static_assert(GS % 2 == 0 && NG >= KC, "groups hold whole entry pairs");
+        const uint32_t vbase = (uint32_t)x0 + (uint32_t)((PP ? pp_row(wx, 0) : wx * 32 * C::MI) +
+                                                         4 * (lane >> 5));
+        // offset from vbase of entry j (block j / 16, register j % 16)
+        auto voff = [](int j) {
+            return (PP ? pp_row(0, j >> 4) : (j >> 4) * 32) + 8 * ((j & 15) >> 2) + (j & 3);
+        };
+        // entries [q EC, q EC + EC) of row ni into this thread's LDS column
+        auto stage = [&](int ni, int q) {
+#pragma unroll
+            for (int j = 0; j < EC; ++j)
+                scr[j * C::NT] = acc_reread(acc[(q * EC + j) >> 4][ni][j & 15]);
+        };
+        // The vocabulary's last tile may run past V (once per chunk at
+        // most): entries at offsets >= lim do not exist.
+        const bool ragged = x0 + C::TX > V;
+        const int lim = ragged ? (int)(V - (int64_t)vbase) : 1 << 30;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            // Alg. 3: move the reference to a maximum that passes it by more
+            // than kLazy.
+            auto raise = [&](float tm) {
+                if (tm > sr[ni] + kLazy) {
+                    dacc[ni] *= exp2_hw(sr[ni] - tm);
+                    sr[ni] = tm;
                 }
             };
-            // entries [q EC, q EC + EC) of row ni into this thread's LDS column
-            auto stage = [&](int ni, int q) {
-#pragma unroll
-                for (int j = 0; j < EC; ++j)
-                    scr[j * C::NT] = acc_reread(acc[(q * EC + j) >> 4][ni][j & 15]);
-            };
-            // The vocabulary's last tile may run past V (once per chunk at
-            // most): entries at offsets >= lim do not exist.
-            const bool ragged = x0 + C::TX > V;
-            const int lim = ragged ? (int)(V - vbase) : 1 << 30;
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                // 1. One pass over the row's entries (the only code unrolled
-                //    over them): the maxima of groups of GS, the terms against
-                //    the current reference and the entries below the list's
-                //    K-th value (tval only rises, so every entry that can still
-                //    enter the list is outside that set).
+            // 1. The chunk's first tile (and the ragged one): the maxima of
+            //    groups of GS entries.  They set the reference, and a first
+            //    threshold: they are entries of distinct groups, so the K-th
+            //    largest of the maxima of this lane and of the other lane
+            //    holding the row is a value that at least K entries reach.
+            if (ragged || __builtin_amdgcn_ballot_w64(sr[ni] == kEmptyS) != 0) {
                 float bm[NG];
-                float dsum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                uint32_t cm[E / 32];
 #pragma unroll
                 for (int g = 0; g < NG; ++g) bm[g] = -__builtin_inff();
 #pragma unroll
-                for (int u = 0; u < E / 32; ++u) cm[u] = 0u;
-                if (!ragged) {
-                    const float th = tval[ni];
-#pragma unroll
-                    for (int j = 0; j < E; j += 2) {
-                        const float a0 = acc_reread(acc[j >> 4][ni][j & 15]);
-                        const float a1 = acc_reread(acc[(j + 1) >> 4][ni][(j + 1) & 15]);
-                        bm[j / GS] = max3_raw(bm[j / GS], a0, a1);
-                        dsum[j & 3] += exp2_hw(__builtin_fmaf(a0, kLog2e, -sr[ni]));
-                        dsum[(j + 1) & 3] += exp2_hw(__builtin_fmaf(a1, kLog2e, -sr[ni]));
-                        cm[j >> 5] |= below_bit(a0, th, j & 31) | below_bit(a1, th, (j + 1) & 31);
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < E; ++j) {
-                        const float a = acc_reread(acc[j >> 4][ni][j & 15]);
-                        bm[j / GS] = __builtin_fmaxf(bm[j / GS], voff(j) < lim ? a : -__builtin_inff());
-                    }
+                for (int j = 0; j < E; ++j) {
+                    const float x = acc_reread(acc[j >> 4][ni][j & 15]);
+                    bm[j / GS] =
+                        __builtin_fmaxf(bm[j / GS], voff(j) < lim ? x : -__builtin_inff());
                 }
+                LaneVals<KC> best;
+                best.init(K);
                 float lm = bm[0];
 #pragma unroll
-                for (int g = 1; g < NG; ++g) lm = __builtin_fmaxf(lm, bm[g]);
-                // 2. Alg. 3: move the reference when some lane's maximum
-                //    passes it by more than kLazy (the chunk's first tile, then
-                //    rarely); the terms are then summed again below.
-                bool recompute = ragged;
-                const float tm = lm * kLog2e;
-                if (__builtin_amdgcn_ballot_w64(tm > sr[ni] + kLazy) != 0) {
-                    if (tm > sr[ni] + kLazy) {
-                        dacc[ni] *= exp2_hw(sr[ni] - tm);
-                        sr[ni] = tm;
-                    }
+                for (int g = 0; g < NG; ++g) {
+                    best.insert(bm[g]);
+                    best.insert(__shfl_xor(bm[g], 32));
+                    lm = __builtin_fmaxf(lm, bm[g]);
+                }
+                raise(lm * kLog2e);
+                tval[ni] = __builtin_fmaxf(tval[ni], best.kth());
+            }
+            // 2. One pass over the row's entries: their maximum, the terms
+            //    against the reference, and the entries that reach the
+            //    threshold, which only rises, so that every entry that can
+            //    still enter the list is among them.
+            float dsum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            uint32_t cm[E / 32];
+#pragma unroll
+            for (int u = 0; u < E / 32; ++u) cm[u] = 0u;
+            bool recompute = ragged;
+            if (!ragged) {
+                const float th = tval[ni];
+                float lm = -__builtin_inff();
+#pragma unroll
+                for (int j = 0; j < E; j += 2) {
+                    const float a0 = acc_reread(acc[j >> 4][ni][j & 15]);
+                    const float a1 = acc_reread(acc[(j + 1) >> 4][ni][(j + 1) & 15]);
+                    lm = max3_raw(lm, a0, a1);
+                    dsum[j & 3] += exp2_hw(__builtin_fmaf(a0, kLog2e, -sr[ni]));
+                    dsum[(j + 1) & 3] += exp2_hw(__builtin_fmaf(a1, kLog2e, -sr[ni]));
+                    push_bit(cm[j >> 5], a0, th);
+                    push_bit(cm[j >> 5], a1, th);
+                }
+                // a move of the reference: the terms are summed again below
+                if (__builtin_amdgcn_ballot_w64(lm * kLog2e > sr[ni] + kLazy) != 0) {
+                    raise(lm * kLog2e);
                     recompute = true;
                 }
-                // 3. A chunk's first tile: the list is empty and every entry
-                //    would be a candidate.  The group maxima are entries of
-                //    distinct groups, so their K-th largest value (ties counted
-                //    once, which only lowers it) is a value that at least K of
-                //    the lane's entries reach: a valid threshold, shared with
-                //    the other lane holding the row.  The candidates are then
-                //    found again below.
-                bool remask = ragged;
-                if (__builtin_amdgcn_ballot_w64(tval[ni] == -__builtin_inff()) != 0) {
-                    if (K <= NG && tval[ni] == -__builtin_inff()) {
-                        float b[NG], boot = -__builtin_inff();
-#pragma unroll
-                        for (int g = 0; g < NG; ++g) b[g] = bm[g];
-#pragma unroll 1
-                        for (int r = 0; r < K; ++r) {
-                            float m = b[0];
-#pragma unroll
-                            for (int g = 1; g < NG; ++g) m = __builtin_fmaxf(m, b[g]);
-#pragma unroll
-                            for (int g = 0; g < NG; ++g) b[g] = b[g] == m ? -__builtin_inff() : b[g];
-                            boot = m;
-                        }
-                        tval[ni] = boot;
-                    }
-                    tval[ni] = __builtin_fmaxf(tval[ni], __shfl_xor(tval[ni], 32));
-                    remask = true;
-                }
-                float ds = recompute ? 0.0f : (dsum[0] + dsum[1]) + (dsum[2] + dsum[3]);
-                // 4. Per part of EC entries, when anything is left to do, the
-                //    part goes to this thread's column of the free LDS stage
-                //    (the one copy of the part's registers in the code), and
-                //    rolled loops finish the work: the terms again after a
-                //    move of the reference, the candidates again after the
-                //    bootstrap or on the ragged tile (with the bound), then
-                //    Alg. 4's insertion of each candidate.
-#pragma unroll
-                for (int q = 0; q < E / EC; ++q) {
-                    uint64_t m = 0;  // candidates of this part
-                    if constexpr (EC >= 32) {
-#pragma unroll
-                        for (int u = 0; u < EC / 32; ++u)
-                            m |= (uint64_t)~cm[q * (EC / 32) + u] << (32 * u);
-                    } else {
-                        m = (~cm[q * EC / 32] >> (q * EC % 32)) & ((1u << EC) - 1u);
-                    }
-                    if (!recompute && !remask && __builtin_amdgcn_ballot_w64(m != 0) == 0) continue;
-                    stage(ni, q);
-                    if (recompute || remask) {
-                        const float tv = tval[ni], s = sr[ni];
-                        uint64_t nm = 0;
-                        float pd = 0.0f;
-#pragma unroll 4
-                        for (int j = 0; j < EC; ++j) {
-                            const float xv = scr[j * C::NT];
-                            const bool valid = voff(q * EC + j) < lim;
-                            const float e = exp2_hw(__builtin_fmaf(xv, kLog2e, -s));
-                            pd += valid ? e : 0.0f;
-                            nm |= (uint64_t)(valid && xv >= tv) << j;
-                        }
-                        if (recompute) ds += pd;
-                        if (remask) m = nm;
-                    }
-                    while (m != 0) {
-                        const int j = __builtin_ctzll(m);
-                        m &= m - 1;
-                        const float xv = scr[j * C::NT];
-                        // a -inf logit is never a candidate
-                        if (xv >= tval[ni] && xv > -__builtin_inff()) offer(ni, xv, q * EC + j);
-                    }
-                }
-                dacc[ni] += ds;
-                // The other lane holding this row saw other entries of it:
-                // the larger of the two K-th values also bounds the row's
-                // K-th value from below.
-                tval[ni] = __builtin_fmaxf(tval[ni], __shfl_xor(tval[ni], 32));
             }
-        });
+            float ds = recompute ? 0.0f : (dsum[0] + dsum[1]) + (dsum[2] + dsum[3]);
+            // 3. Per part of EC entries, when anything is left to do, the
+            //    part goes to this thread's LDS column (the one copy of the
+            //    part's registers in the code), and rolled loops finish the
+            //    work: the terms again after a move of the reference, with
+            //    the bound on the ragged tile, whose candidates are found
+            //    here too, then Alg. 4's insertion of each candidate.
+#pragma unroll
+            for (int q = 0; q < E / EC; ++q) {
+                // candidates of this part, the first in the highest bit
+                uint64_t m;
+                if constexpr (EC == 64)
+                    m = (uint64_t)cm[2 * q] << 32 | cm[2 * q + 1];
+                else if constexpr (EC == 32)
+                    m = (uint64_t)cm[q] << 32;
+                else
+                    m = (uint64_t)(q % 2 == 0 ? cm[q / 2] >> 16 : cm[q / 2] & 0xFFFFu) << 48;
+                if (!recompute && __builtin_amdgcn_ballot_w64(m != 0) == 0) continue;
+                stage(ni, q);
+                if (recompute) {
+                    const float tv = tval[ni], s = sr[ni];
+                    uint64_t nm = 0;
+                    float pd = 0.0f;
+#pragma unroll 4
+                    for (int j = 0; j < EC; ++j) {
+                        const float xv = scr[j * C::NT];
+                        const bool valid = voff(q * EC + j) < lim;
+                        const float e = exp2_hw(__builtin_fmaf(xv, kLog2e, -s));
+                        pd += valid ? e : 0.0f;
+                        nm |= (uint64_t)(valid && xv >= tv) << (63 - j);
+                    }
+                    ds += pd;
+                    if (ragged) m = nm;
+                }
+                while (m != 0) {
+                    const int j = __builtin_clzll(m);
+                    m &= ~(0x8000000000000000ull >> j);
+                    list[ni].insert(scr[j * C::NT], vbase + (uint32_t)voff(q * EC + j));
+                }
+            }
+            dacc[ni] += ds;
+            // An entry equal to this lane's K-th value comes after the list's
+            // (a higher index), so only larger ones count from here on; the
+            // other lane holding the row saw other entries, so its K-th value
+            // only bounds the row's from below.
+            const float own = list[ni].l.kth();
+            tval[ni] = __builtin_fmaxf(
+                tval[ni], __builtin_fmaxf(next_up(own), __shfl_xor(own, 32)));
+        }
+    };
+    if constexpr (PP) pp_run<C>(w, V, h, N, H, t0, t1, sm.st, coords, epi);
+    else pj_run<C>(w, V, h, N, H, t0, t1, sm, coords, epi);
 
     constexpr int P = 2 * C::WX;  // partials per (row, chunk)
     const int64_t Sp = S * P;
     const int64_t p = c * P + wx * 2 + (lane >> 5);
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
-        const int64_t row = y0s + wy * 32 * NI + ni * 32 + (lane & 31);
+        const int64_t row = y0s + (PP ? pp_col(wy, ni) : wy * 32 * NI + ni * 32) + (lane & 31);
         if (row < N) {
-            uint64_t* dst = pkeys + (row * Sp + p) * K;
+            uint64_t* dst = pkeys + (row * Sp + p) * K - (KC - K);
 #pragma unroll
             for (int i = 0; i < KC; ++i)
-                if (i < K) dst[i] = list[ni].L[i];
+                if (i >= KC - K) dst[i] = list[ni].key(i);
             pmd[row * Sp + p] = MD{sr[ni], dacc[ni]};
         }
     }
@@ -478,14 +489,14 @@ size_t proj_topk_part_bytes(int64_t N, int64_t S, int parts, int K) {
     return (size_t)N * (size_t)(S * parts) * ((size_t)K * 8 + 8);
 }
 
-template <class C, int KC>
+template <class C, int KC, bool PP = false>
 static void launch_part(const void* h, const void* w, uint64_t* pkeys, MD* pmd, int64_t N,
                         int64_t H, int64_t V, int K, int64_t S, int64_t tiles, hipStream_t st) {
     const int64_t nb = (N + C::TY - 1) / C::TY;
     const int64_t sb = nb < PJ_SB ? nb : PJ_SB, nsb = (nb + sb - 1) / sb;
     const int64_t ids = (S + PJ_CB - 1) / PJ_CB * nsb * PJ_CB * sb;  // whole blocks
     const int64_t per = (ids + 7) / 8;
-    hipLaunchKernelGGL((proj_topk_part<C, KC>), dim3((unsigned)(8 * per)), dim3(C::NT), 0,
+    hipLaunchKernelGGL((proj_topk_part<C, KC, PP>), dim3((unsigned)(8 * per)), dim3(C::NT), 0,
                        st, (const uint16_t*)h, (const uint16_t*)w, pkeys, pmd, N, H, V, K, S,
                        tiles, per);
 }
@@ -498,7 +509,7 @@ hipError_t launch_proj_topk(const void* h, const void* w, float* vals, int32_t* 
     MD* pmd = reinterpret_cast<MD*>(pkeys + N * Sp * K);
     const int cfg = fused_cfg(N, K);
     if (cfg == 0)
-        launch_part<PjFused8, 8>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+        launch_part<PjFused8, 8, true>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
     else if (cfg == 1)
         launch_part<PjFused16W, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
     else if (cfg == 2)
