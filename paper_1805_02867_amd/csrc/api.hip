@@ -553,17 +553,15 @@ int run_proj_topk(const void* h, const void* w, float* vals, int32_t* idx, int64
         return OSM_EINVAL;
     DeviceState* ds = device_state(nullptr);
     if (!ds) return OSM_EHIP;
-    int64_t S = 1, tiles = 1;
-    int parts = 2;
-    osm::proj_topk_shape(N, V, K, ds->cus, &S, &tiles, &parts);
+    const osm::ProjTopkShape p = osm::proj_topk_shape(N, H, V, K, ds->cus);
     void* part = nullptr;
     bool temp = false;
     std::unique_lock<std::mutex> lk(ds->mu, std::defer_lock);  // held until the launches are in
-    st = acquire_scratch(ds, lk, stream, osm::proj_topk_part_bytes(N, S, parts, K), &part,
+    st = acquire_scratch(ds, lk, stream, osm::proj_topk_part_bytes(N, p.S, p.parts, K), &part,
                          &temp);
     if (st != OSM_OK) return st;
     hipError_t e =
-        osm::launch_proj_topk(h, w, vals, idx, part, N, H, V, K, S, tiles, parts, stream);
+        osm::launch_proj_topk(h, w, vals, idx, part, N, H, V, K, p, stream);
     hipError_t f = temp ? hipFreeAsync(part, stream) : hipSuccess;
     if (e != hipSuccess) return OSM_EHIP;
     return hip_status(f);

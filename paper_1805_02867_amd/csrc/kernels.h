@@ -29,16 +29,20 @@ hipError_t launch_softmax_resident(const void* x, void* y, int64_t N, int64_t V,
 hipError_t launch_proj_logits(const void* h, const void* w, float* out, int64_t N, int64_t H,
                               int64_t V, int cus, hipStream_t st);
 
-// Projection fused with the online softmax and top-k: S vocabulary chunks of
-// `tiles` tiles each, `parts` partials per (row, chunk) (proj_topk_shape
-// picks all three for a device with `cus` compute units); part holds
+// Projection fused with the online softmax and top-k: the kernel layout, S
+// vocabulary chunks of `tiles` tiles each, and `parts` partials per (row,
+// chunk), for a device with `cus` compute units.  part holds
 // proj_topk_part_bytes(N, S, parts, K) bytes.
-void proj_topk_shape(int64_t N, int64_t V, int K, int cus, int64_t* S, int64_t* tiles,
-                     int* parts);
+struct ProjTopkShape {
+    int cfg;
+    int64_t S, tiles;
+    int parts;
+};
+ProjTopkShape proj_topk_shape(int64_t N, int64_t H, int64_t V, int K, int cus);
 size_t proj_topk_part_bytes(int64_t N, int64_t S, int parts, int K);
 hipError_t launch_proj_topk(const void* h, const void* w, float* vals, int32_t* idx,
-                            void* part, int64_t N, int64_t H, int64_t V, int K, int64_t S,
-                            int64_t tiles, int parts, hipStream_t st);
+                            void* part, int64_t N, int64_t H, int64_t V, int K,
+                            const ProjTopkShape& p, hipStream_t st);
 
 // Reference streaming kernels (measurement only): op 0 reads `vecs` 16-byte
 // vectors of x (y: a 1 KB sink, written only for a sum never met), op 1

@@ -34,8 +34,13 @@ using PjSmall = PjCfg<128, 128, 2, 2>;
 //    loop), so two wavefronts share each SIMD.  Projection + top-5, us, against
 //    the same epilogue's forerunner on pj_run: 4000 x 4096 x 32000 950 -> 875,
 //    4000 x 1024 x 32000 384 -> 307, 512 x 4096 x 128256 566 -> 494;
-//  * 256 x 128 in 2 x 4 wavefronts (8 < K <= 16, N > 1024): one batch row per
-//    lane, also two wavefronts per SIMD;
+//    also for 8 < K <= 16 where the products outweigh the longer lists'
+//    epilogue (H >= 2048, and at least two tiles a workgroup: 4000 x 4096 x
+//    32000 top-16 1300 -> 1000 us, 1000 x 4096 x 32000 351 -> 297, 4000 x 2048
+//    x 32000 630 -> 605; but 4000 x 1024 x 32000 365 -> 408, and in one tile a
+//    workgroup 512 x 2048 x 32000 107 -> 118);
+//  * 256 x 128 in 2 x 4 wavefronts (8 < K <= 16, N > 1024 otherwise): one batch
+//    row per lane, also two wavefronts per SIMD;
 //  * 256 x 128 in 1 x 4 wavefronts (otherwise, N > 64): one batch row per
 //    lane, one wavefront per SIMD, measured faster than the 2 x 4 layout up
 //    to N = 512;
@@ -45,10 +50,15 @@ using PjFused8 = PjCfg<256, 256, 2, 4>;
 using PjFused16W = PjCfg<256, 128, 2, 4>;
 using PjFused16 = PjCfg<256, 128, 1, 4>;
 using PjFusedN = PjCfg<256, 64, 2, 2>;
-static int fused_cfg(int64_t N, int K) {
-    if (N <= 64) return 3;
-    if (K <= 8 && N > 128) return 0;
-    return K > 8 && N > 1024 ? 1 : 2;
+enum FusedCfg { FUSED_8, FUSED_16, FUSED_16W, FUSED_16T, FUSED_N };
+static FusedCfg fused_cfg(int64_t N, int64_t H, int64_t V, int K, int cus) {
+    if (N <= 64) return FUSED_N;
+    if (N > 128) {
+        if (K <= 8) return FUSED_8;
+        const int64_t tiles = ((N + 255) / 256) * ((V + 255) / 256);
+        if (H >= 2048 && tiles > cus) return FUSED_16;
+    }
+    return N > 1024 ? FUSED_16W : FUSED_16T;
 }
 
 // ------------------------------------------------------------ plain logits
@@ -269,7 +279,12 @@ __global__ __launch_bounds__(C::NT) void proj_topk_part(
     for (int ni = 0; ni < NI; ++ni) {
         sr[ni] = kEmptyS;
         dacc[ni] = 0.0f;
-        tval[ni] = -__builtin_inff();
+        // Lanes of rows past the batch take no candidates: their logits are all
+        // zero, and so many ties cost more than a real row's candidates
+        // (100 x 1024 x 32000 top-5: 55.6 us with them, 33.5 without;
+        // 300 x 512 x 20000: 57.2 and 39.2).
+        const int64_t row = y0s + (PP ? pp_col(wy, ni) : wy * 32 * NI + ni * 32) + (lane & 31);
+        tval[ni] = row < N ? -__builtin_inff() : __builtin_inff();
         list[ni].init(K);
     }
     float* scr;  // this thread's column
@@ -458,31 +473,27 @@ hipError_t launch_proj_logits(const void* h, const void* w, float* out, int64_t 
     return launch_logits_t<PjSmall, false>(h, w, out, N, H, V, st);
 }
 
-void proj_topk_shape(int64_t N, int64_t V, int K, int cus, int64_t* S, int64_t* tiles,
-                     int* parts) {
-    const int cfg = fused_cfg(N, K);
-    const int64_t TY = cfg == 0 ? PjFused8::TY
-                       : cfg == 1 ? PjFused16W::TY
-                       : cfg == 2 ? PjFused16::TY
-                                  : PjFusedN::TY;
+ProjTopkShape proj_topk_shape(int64_t N, int64_t H, int64_t V, int K, int cus) {
+    const FusedCfg cfg = fused_cfg(N, H, V, K, cus);
     const int64_t TX = PjFused8::TX;
-    *parts = 2 * (cfg == 0 ? PjFused8::WX
-                  : cfg == 1 ? PjFused16W::WX
-                  : cfg == 2 ? PjFused16::WX
-                             : PjFusedN::WX);
+    const int64_t TY = cfg == FUSED_8 || cfg == FUSED_16 ? PjFused8::TY
+                       : cfg == FUSED_N                  ? PjFusedN::TY
+                                                         : PjFused16::TY;
+    static_assert(PjFused16::TY == PjFused16W::TY, "one strip height for the 256 x 128 tiles");
+    static_assert(PjFused8::WX == 2 && PjFused16W::WX == 2 && PjFusedN::WX == 2 && PjFused16::WX == 1,
+                  "partials per (row, chunk): 2 WX");
     // vocabulary chunks: about one workgroup per CU in all (each takes 80 KB
     // of LDS or more); two per CU for the 256 x 64 tiles at K <= 8 (80 KB
     // each, both fit), where the call streams w and twice the loads in
     // flight pay for the merge of twice the partials (measured 5-7% faster
     // at N <= 64; at K = 16 the larger merge ate the gain)
     const int64_t nb = (N + TY - 1) / TY, nt = (V + TX - 1) / TX;
-    const int64_t per_cu = cfg == 3 && K <= 8 ? 2 : 1;
+    const int64_t per_cu = cfg == FUSED_N && K <= 8 ? 2 : 1;
     int64_t s = ((int64_t)cus * per_cu + nb - 1) / nb;
     if (s > nt) s = nt;
     if (s < 1) s = 1;
     const int64_t t = (nt + s - 1) / s;
-    *tiles = t;
-    *S = (nt + t - 1) / t;
+    return {cfg, (nt + t - 1) / t, t, cfg == FUSED_16T ? 2 : 4};
 }
 
 size_t proj_topk_part_bytes(int64_t N, int64_t S, int parts, int K) {
@@ -502,20 +513,27 @@ static void launch_part(const void* h, const void* w, uint64_t* pkeys, MD* pmd, 
 }
 
 hipError_t launch_proj_topk(const void* h, const void* w, float* vals, int32_t* idx,
-                            void* part, int64_t N, int64_t H, int64_t V, int K, int64_t S,
-                            int64_t tiles, int parts, hipStream_t st) {
-    const int64_t Sp = S * parts;  // partials per row
+                            void* part, int64_t N, int64_t H, int64_t V, int K,
+                            const ProjTopkShape& p, hipStream_t st) {
+    const int64_t S = p.S, tiles = p.tiles, Sp = S * p.parts;  // partials per row
     uint64_t* pkeys = static_cast<uint64_t*>(part);
     MD* pmd = reinterpret_cast<MD*>(pkeys + N * Sp * K);
-    const int cfg = fused_cfg(N, K);
-    if (cfg == 0)
-        launch_part<PjFused8, 8, true>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
-    else if (cfg == 1)
-        launch_part<PjFused16W, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
-    else if (cfg == 2)
-        launch_part<PjFused16, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
-    else
-        launch_part<PjFusedN, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+    switch (p.cfg) {
+        case FUSED_8:
+            launch_part<PjFused8, 8, true>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+            break;
+        case FUSED_16:
+            launch_part<PjFused8, 16, true>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+            break;
+        case FUSED_16W:
+            launch_part<PjFused16W, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+            break;
+        case FUSED_16T:
+            launch_part<PjFused16, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+            break;
+        default:
+            launch_part<PjFusedN, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_merge_held<TK_ONLINE>(pkeys, pmd, vals, idx, N, Sp, K, st);
