@@ -232,8 +232,26 @@ Plan choose(int64_t N, int64_t V, int dtype, int cus) {
     // about four chunks per CU in all, six for the smallest batches (at 10
     // rows of 10^6: 19.5 us with six against 22.5 with four; at 64 or 256
     // rows four is as fast or faster).
+    //
+    // A workgroup per row is faster for rows of up to 20480 elements, and for
+    // up to 57344 (24576 in bfloat16, which brings twice the arithmetic per
+    // byte to one CU) once three CUs in eight have a row (us, a workgroup per
+    // row against the split: 64 x 16384 binary32 5.1 / 6.1, 200 x 32000 11.3 /
+    // 15.1, 300 x 20481 bfloat16 9.2 / 11.2). Longer rows need half of the CUs
+    // busy, three quarters for the longest bfloat16 ones (130 x 100000 binary32
+    // 24.1 / 28.5, but 96 x 66001 16.1 / 15.4; bfloat16 130 x 50257 10.5 / 12.6,
+    // but 96 x 32000 8.5 / 7.8 and 160 x 100000 21.3 / 18.8); no second round
+    // of rows that only some CUs take (300 x 57344 bfloat16 19.4 / 17.3, but
+    // 511 x 57344 25.0 / 32.5); and a second pass that still finds most of the
+    // row in cache (150 x 150001 binary32 50.9 / 47.1).
     const int64_t want_blocks = (N <= 16 ? 6 : 4) * (int64_t)cus;
-    if (N < 2 * (int64_t)cus && V >= 16384) {
+    const bool f32 = dtype == OSM_F32;
+    const bool busy = f32 || V <= 57344 ? 2 * N >= cus : 4 * N >= 3 * (int64_t)cus;
+    const bool even = N <= cus || 5 * N >= 8 * (int64_t)cus;
+    const bool rows = V <= 20480 || (V <= (f32 ? 57344 : 24576) && 8 * N >= 3 * (int64_t)cus) ||
+                      (V <= 131072 && busy && even);
+    if (N < 2 * (int64_t)cus && rows && nv > 2048 && nv <= 6144) return {OSM_KERNEL_ROWS, 512};
+    if (N < 2 * (int64_t)cus && !rows) {
         int64_t S = (want_blocks + N - 1) / N;
         int64_t s_cap = (V + 4095) / 4096;  // keep chunks >= 4096 elements
         if (S > s_cap) S = s_cap;

@@ -1,0 +1,36 @@
+"""The softmax plan's line between a workgroup per row and split rows, on both
+of its sides: the plan says which kernel runs, and its output matches the
+binary64 oracle, on rows with a heavy tail, an equal row and mostly -inf."""
+import pytest
+import torch
+
+import oracle
+import paper_1805_02867_amd as osm
+from paper_1805_02867_amd import synth
+from parity import assert_softmax_close, host_dtype, to_host
+
+pytestmark = pytest.mark.gpu
+
+R, S = osm.KERNEL_ROWS, osm.KERNEL_SPLIT
+
+
+@pytest.mark.parametrize("N,V,dtype,kernel", [
+    (2, 16384, "f32", R), (2, 20480, "bf16", R), (2, 20481, "f32", S), (95, 20481, "bf16", S),
+    (96, 20481, "f32", R), (96, 57344, "f32", R), (96, 57345, "f32", S), (128, 57345, "f32", R),
+    (256, 131071, "f32", R), (257, 57345, "f32", S), (128, 131073, "f32", S),
+    (96, 24576, "bf16", R), (96, 24577, "bf16", S), (128, 24577, "bf16", R), (191, 57345, "bf16", S),
+    (192, 57345, "bf16", R), (300, 24577, "bf16", S), (410, 24577, "bf16", R), (511, 16385, "bf16", R),
+])
+def test_plan_line(N, V, dtype, kernel):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the batch sizes stand for 256 CUs")
+    x = synth.logits(N, V, sigma=3.0, seed=V + N, dtype=dtype, device="cuda")
+    x[0, 1:] = float("-inf")
+    x[1] = 0.5
+    for mode in ("naive", "safe", "online"):
+        print(f"{N}x{V} {dtype} {mode}", flush=True)
+        assert osm.plan(N, V, dtype=x.dtype, mode=mode)[0] == kernel
+        y = osm.softmax_fwd(x, mode=mode)
+        pick = [0, 1, N // 2, N - 1]
+        assert_softmax_close(to_host(y[pick]), oracle.softmax(to_host(x[pick]), host_dtype(x)),
+                             f"{N}x{V} {dtype} {mode}")
