@@ -97,7 +97,7 @@ __device__ __forceinline__ void store_block(const f32x16& acc, float* __restrict
     }
 }
 
-template <class C>
+template <class C, int WA>
 __global__ __launch_bounds__(C::NT) void proj_logits(const uint16_t* __restrict__ h,
                                                      const uint16_t* __restrict__ w,
                                                      float* __restrict__ out, int64_t N,
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(C::NT) void proj_logits(const uint16_t* __restrict_
     int64_t bx0, vy0;
     if (!logits_tile<C>(N, V, per, bx0, vy0)) return;  // the whole workgroup leaves
     const int wave = threadIdx.x >> 6, wx = wave / C::WY, wy = wave % C::WY;
-    pj_run<C>(
+    pj_run<C, 0, WA>(
         h, N, w, V, H, 0, 1, sm,
         [&](int64_t, int64_t& x0, int64_t& y0) {
             x0 = bx0;
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(C::NT) void proj_logits_pp(const uint16_t* __restri
     int64_t bx0, vy0;
     if (!logits_tile<C>(N, V, per, bx0, vy0)) return;  // the whole workgroup leaves
     const int wave = pj_wave(), wx = wave / C::WY, wy = wave % C::WY;
-    pp_run<C>(
+    pp_run<C, 0>(
         h, N, w, V, H, 0, 1, sm,
         [&](int64_t, int64_t& x0, int64_t& y0) {
             x0 = bx0;
@@ -237,7 +237,8 @@ struct LaneList {
 // pair and K keys (0 = none).
 // PP: the two-group core (256 x 256), whose stages stay in use during the
 // epilogue, so that the epilogue's columns get the LDS that the stages leave.
-template <class C, int KC, bool PP>
+// WA: cache policy of the vocabulary's loads.
+template <class C, int KC, bool PP, int WA>
 __global__ __launch_bounds__(C::NT) void proj_topk_part(
     const uint16_t* __restrict__ h, const uint16_t* __restrict__ w, uint64_t* __restrict__ pkeys,
     MD* __restrict__ pmd, int64_t N, int64_t H, int64_t V, int K, int64_t S, int64_t tiles,
@@ -432,8 +433,8 @@ __global__ __launch_bounds__(C::NT) void proj_topk_part(
                 tval[ni], __builtin_fmaxf(next_up(own), __shfl_xor(own, 32)));
         }
     };
-    if constexpr (PP) pp_run<C>(w, V, h, N, H, t0, t1, sm.st, coords, epi);
-    else pj_run<C>(w, V, h, N, H, t0, t1, sm, coords, epi);
+    if constexpr (PP) pp_run<C, WA>(w, V, h, N, H, t0, t1, sm.st, coords, epi);
+    else pj_run<C, WA, 0>(w, V, h, N, H, t0, t1, sm, coords, epi);
 
     constexpr int P = 2 * C::WX;  // partials per (row, chunk)
     const int64_t Sp = S * P;
@@ -452,7 +453,18 @@ __global__ __launch_bounds__(C::NT) void proj_topk_part(
 }
 
 // ---------------------------------------------------------------- launchers
-template <class C, bool PP>
+// Whether w is read once, by one strip of `rows` batch rows, and the last-level
+// cache (256 MB) could not keep enough of it for the next call (us, PJ_ONCE
+// against the default: projection + top-5 64 x 4096 x 128256 167 / 186, 100 x
+// ... 213 / 229, 200 x ... 257 / 270, 64 x 4096 x 50000 109 / 116; logits 64 x
+// 4096 x 128256 168 / 177; but on the same w again 64 x 2048 x 68000, 279 MB,
+// 84 / 68, and with more strips, which share w in L2, 768 x 4096 x 128256 750 /
+// 730).  The logits' 256 x 256 tiles gain nothing (256 x 4096 x 128256 345 / 345).
+static bool w_once(int64_t N, int64_t H, int64_t V, int64_t rows) {
+    return N <= rows && V * H * 2 >= ((int64_t)384 << 20);
+}
+
+template <class C, bool PP, int WA>
 static hipError_t launch_logits_t(const void* h, const void* w, float* out, int64_t N, int64_t H,
                                   int64_t V, hipStream_t st) {
     const int64_t total = ((N + C::TX - 1) / C::TX) * ((V + C::TY - 1) / C::TY);
@@ -461,7 +473,7 @@ static hipError_t launch_logits_t(const void* h, const void* w, float* out, int6
         hipLaunchKernelGGL((proj_logits_pp<C>), dim3((unsigned)(8 * per)), dim3(C::NT), 0, st,
                            (const uint16_t*)h, (const uint16_t*)w, out, N, H, V, per);
     else
-        hipLaunchKernelGGL((proj_logits<C>), dim3((unsigned)(8 * per)), dim3(C::NT), 0, st,
+        hipLaunchKernelGGL((proj_logits<C, WA>), dim3((unsigned)(8 * per)), dim3(C::NT), 0, st,
                            (const uint16_t*)h, (const uint16_t*)w, out, N, H, V, per);
     return hipGetLastError();
 }
@@ -469,8 +481,10 @@ static hipError_t launch_logits_t(const void* h, const void* w, float* out, int6
 hipError_t launch_proj_logits(const void* h, const void* w, float* out, int64_t N, int64_t H,
                               int64_t V, int cus, hipStream_t st) {
     const int64_t big = ((N + PjBig::TX - 1) / PjBig::TX) * ((V + PjBig::TY - 1) / PjBig::TY);
-    if (big >= 2 * (int64_t)cus) return launch_logits_t<PjBig, true>(h, w, out, N, H, V, st);
-    return launch_logits_t<PjSmall, false>(h, w, out, N, H, V, st);
+    if (big >= 2 * (int64_t)cus) return launch_logits_t<PjBig, true, 0>(h, w, out, N, H, V, st);
+    if (w_once(N, H, V, PjSmall::TX))
+        return launch_logits_t<PjSmall, false, PJ_ONCE>(h, w, out, N, H, V, st);
+    return launch_logits_t<PjSmall, false, 0>(h, w, out, N, H, V, st);
 }
 
 ProjTopkShape proj_topk_shape(int64_t N, int64_t H, int64_t V, int K, int cus) {
@@ -500,14 +514,14 @@ size_t proj_topk_part_bytes(int64_t N, int64_t S, int parts, int K) {
     return (size_t)N * (size_t)(S * parts) * ((size_t)K * 8 + 8);
 }
 
-template <class C, int KC, bool PP = false>
+template <class C, int KC, bool PP, int WA>
 static void launch_part(const void* h, const void* w, uint64_t* pkeys, MD* pmd, int64_t N,
                         int64_t H, int64_t V, int K, int64_t S, int64_t tiles, hipStream_t st) {
     const int64_t nb = (N + C::TY - 1) / C::TY;
     const int64_t sb = nb < PJ_SB ? nb : PJ_SB, nsb = (nb + sb - 1) / sb;
     const int64_t ids = (S + PJ_CB - 1) / PJ_CB * nsb * PJ_CB * sb;  // whole blocks
     const int64_t per = (ids + 7) / 8;
-    hipLaunchKernelGGL((proj_topk_part<C, KC, PP>), dim3((unsigned)(8 * per)), dim3(C::NT), 0,
+    hipLaunchKernelGGL((proj_topk_part<C, KC, PP, WA>), dim3((unsigned)(8 * per)), dim3(C::NT), 0,
                        st, (const uint16_t*)h, (const uint16_t*)w, pkeys, pmd, N, H, V, K, S,
                        tiles, per);
 }
@@ -518,21 +532,26 @@ hipError_t launch_proj_topk(const void* h, const void* w, float* vals, int32_t* 
     const int64_t S = p.S, tiles = p.tiles, Sp = S * p.parts;  // partials per row
     uint64_t* pkeys = static_cast<uint64_t*>(part);
     MD* pmd = reinterpret_cast<MD*>(pkeys + N * Sp * K);
+    auto part_of = [&](auto cfg, auto kc, auto pp, auto wa) {
+        launch_part<decltype(cfg), decltype(kc)::value, decltype(pp)::value, decltype(wa)::value>(
+            h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+    };
+    auto run = [&](auto cfg, auto kc, auto pp) {
+        if (w_once(N, H, V, decltype(cfg)::TY))
+            part_of(cfg, kc, pp, std::integral_constant<int, PJ_ONCE>{});
+        else
+            part_of(cfg, kc, pp, std::integral_constant<int, 0>{});
+    };
+    const std::integral_constant<int, 8> k8;
+    const std::integral_constant<int, 16> k16;
     switch (p.cfg) {
-        case FUSED_8:
-            launch_part<PjFused8, 8, true>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+        case FUSED_8: run(PjFused8{}, k8, std::true_type{}); break;
+        case FUSED_16: run(PjFused8{}, k16, std::true_type{}); break;
+        case FUSED_16W:  // more than one strip: N > 1024
+            part_of(PjFused16W{}, k16, std::false_type{}, std::integral_constant<int, 0>{});
             break;
-        case FUSED_16:
-            launch_part<PjFused8, 16, true>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
-            break;
-        case FUSED_16W:
-            launch_part<PjFused16W, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
-            break;
-        case FUSED_16T:
-            launch_part<PjFused16, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
-            break;
-        default:
-            launch_part<PjFusedN, 16>(h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
+        case FUSED_16T: run(PjFused16{}, k16, std::false_type{}); break;
+        default: run(PjFusedN{}, k16, std::false_type{});
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
