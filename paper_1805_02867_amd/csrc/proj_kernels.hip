@@ -26,7 +26,7 @@ namespace osm {
 // per CU), which keep small problems spread over more CUs.
 using PjBig = PjCfg<256, 256, 2, 4>;
 using PjSmall = PjCfg<128, 128, 2, 2>;
-// Fused, by batch size and K (the vocabulary tile is 256 entries in all; the
+// Fused, by batch size and K (the vocabulary tile is 256 entries past 64 rows; the
 // lanes' top-K lists live in registers):
 //  * 256 x 256 (K <= 8, N > 128): the two-group core's 2 x 4 wavefronts, two
 //    batch rows per lane; 128 result registers and 128 others per lane (the
@@ -44,15 +44,34 @@ using PjSmall = PjCfg<128, 128, 2, 2>;
 //  * 256 x 128 in 1 x 4 wavefronts (otherwise, N > 64): one batch row per
 //    lane, one wavefront per SIMD, measured faster than the 2 x 4 layout up
 //    to N = 512;
-//  * 256 x 64 (N <= 64): 2 x 2 wavefronts, one batch row per lane, so small
-//    batches do not pay for a strip of 256 rows.
+//  * 64 rows of batch (N <= 64), one batch row per lane, so small batches do
+//    not pay for a strip of 256: 256 x 64 in 2 x 2 wavefronts, two workgroups a
+//    CU, for the largest vocabularies; 128 x 64 in 2 x 2 (K <= 8), three a CU,
+//    while those take every tile at once; 64 x 64 in 1 x 2 for small ones, of
+//    which the taller tiles would occupy half of the CUs or fewer.  Projection
+//    + top-5 of 64 or 40 rows, us, in 256, 128 and 64 rows of vocabulary: 4096 x
+//    8192 57.6 / 45.1 / 40.6, 4096 x 32000 77.3 / 66.8 / 63.9, 1024 x 32000 27.0
+//    / 24.2 / 22.2, 4096 x 50257 108 / 96.5 / 106.6, 4096 x 90000 142 / 136 /
+//    150, 4096 x 128256 167 / 175 / 187.  For K > 8 the merge of twice the lists
+//    costs more: 64 x 64 only up to two tiles a CU, and past 16384 only where
+//    the products weigh enough (top-16 of 40 rows, 256 against 64: 4096 x 20000
+//    66.7 / 52.8, 256 x 8192 20.2 / 18.4; but 256 x 32000 22.8 / 24.3).
 using PjFused8 = PjCfg<256, 256, 2, 4>;
 using PjFused16W = PjCfg<256, 128, 2, 4>;
 using PjFused16 = PjCfg<256, 128, 1, 4>;
 using PjFusedN = PjCfg<256, 64, 2, 2>;
-enum FusedCfg { FUSED_8, FUSED_16, FUSED_16W, FUSED_16T, FUSED_N };
+using PjFusedNM = PjCfg<128, 64, 2, 2>;
+using PjFusedNS = PjCfg<64, 64, 1, 2>;
+enum FusedCfg { FUSED_8, FUSED_16, FUSED_16W, FUSED_16T, FUSED_N, FUSED_NM, FUSED_NS };
 static FusedCfg fused_cfg(int64_t N, int64_t H, int64_t V, int K, int cus) {
-    if (N <= 64) return FUSED_N;
+    if (N <= 64) {
+        const int64_t t64 = (V + 63) / 64, t128 = (V + 127) / 128;
+        if (K <= 8)
+            return 2 * t64 <= 5 * (int64_t)cus    ? FUSED_NS
+                   : t128 <= 3 * (int64_t)cus ? FUSED_NM
+                                              : FUSED_N;
+        return t64 <= 2 * (int64_t)cus && (H >= 1024 || t64 <= cus) ? FUSED_NS : FUSED_N;
+    }
     if (N > 128) {
         if (K <= 8) return FUSED_8;
         const int64_t tiles = ((N + 255) / 256) * ((V + 255) / 256);
@@ -489,25 +508,34 @@ hipError_t launch_proj_logits(const void* h, const void* w, float* out, int64_t 
 
 ProjTopkShape proj_topk_shape(int64_t N, int64_t H, int64_t V, int K, int cus) {
     const FusedCfg cfg = fused_cfg(N, H, V, K, cus);
-    const int64_t TX = PjFused8::TX;
-    const int64_t TY = cfg == FUSED_8 || cfg == FUSED_16 ? PjFused8::TY
-                       : cfg == FUSED_N                  ? PjFusedN::TY
-                                                         : PjFused16::TY;
-    static_assert(PjFused16::TY == PjFused16W::TY, "one strip height for the 256 x 128 tiles");
-    static_assert(PjFused8::WX == 2 && PjFused16W::WX == 2 && PjFusedN::WX == 2 && PjFused16::WX == 1,
-                  "partials per (row, chunk): 2 WX");
+    // vocabulary rows of a tile, batch rows of a strip, and partials per (row,
+    // chunk): two for each wavefront along the vocabulary
+    int64_t TX = PjFused8::TX, TY = PjFused8::TY;
+    int parts = 2 * PjFused8::WX;
+    auto of = [&](auto c) { TX = c.TX, TY = c.TY, parts = 2 * c.WX; };
+    switch (cfg) {
+        case FUSED_16W: of(PjFused16W{}); break;
+        case FUSED_16T: of(PjFused16{}); break;
+        case FUSED_N: of(PjFusedN{}); break;
+        case FUSED_NM: of(PjFusedNM{}); break;
+        case FUSED_NS: of(PjFusedNS{}); break;
+        default: break;
+    }
     // vocabulary chunks: about one workgroup per CU in all (each takes 80 KB
-    // of LDS or more); two per CU for the 256 x 64 tiles at K <= 8 (80 KB
-    // each, both fit), where the call streams w and twice the loads in
-    // flight pay for the merge of twice the partials (measured 5-7% faster
-    // at N <= 64; at K = 16 the larger merge ate the gain)
+    // of LDS or more); as many as fit for the tiles of 64 batch rows at K <= 8
+    // and 64 x 64 (80, 48 and 32 KB of LDS), where the call streams w and the
+    // loads in flight pay for the merge of more partials (256 x 64 measured
+    // 5-7% faster at K <= 8; at K = 16 the larger merge ate the gain)
     const int64_t nb = (N + TY - 1) / TY, nt = (V + TX - 1) / TX;
-    const int64_t per_cu = cfg == FUSED_N && K <= 8 ? 2 : 1;
+    const int64_t per_cu = cfg == FUSED_NS             ? 5
+                           : cfg == FUSED_NM           ? 3
+                           : cfg == FUSED_N && K <= 8 ? 2
+                                                      : 1;
     int64_t s = ((int64_t)cus * per_cu + nb - 1) / nb;
     if (s > nt) s = nt;
     if (s < 1) s = 1;
     const int64_t t = (nt + s - 1) / s;
-    return {cfg, (nt + t - 1) / t, t, cfg == FUSED_16T ? 2 : 4};
+    return {cfg, (nt + t - 1) / t, t, parts};
 }
 
 size_t proj_topk_part_bytes(int64_t N, int64_t S, int parts, int K) {
@@ -551,7 +579,14 @@ hipError_t launch_proj_topk(const void* h, const void* w, float* vals, int32_t* 
             part_of(PjFused16W{}, k16, std::false_type{}, std::integral_constant<int, 0>{});
             break;
         case FUSED_16T: run(PjFused16{}, k16, std::false_type{}); break;
-        default: run(PjFusedN{}, k16, std::false_type{});
+        case FUSED_NM: run(PjFusedNM{}, k8, std::false_type{}); break;
+        case FUSED_NS:
+            if (K <= 8) run(PjFusedNS{}, k8, std::false_type{});
+            else run(PjFusedNS{}, k16, std::false_type{});
+            break;
+        default:
+            if (K <= 8) run(PjFusedN{}, k8, std::false_type{});
+            else run(PjFusedN{}, k16, std::false_type{});
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -74,3 +74,13 @@ def test_topk_of_ordered_logits(dev, N, K):
         w[:, 0] = torch.div(order, 128, rounding_mode="floor").to(torch.bfloat16)
         w[:, 1] = (order % 128).to(torch.bfloat16)
         check_topk(h, w, K, f"{what} N={N} K={K}")
+
+
+@pytest.mark.parametrize("K", [1, 8, 9, 16])
+@pytest.mark.parametrize("V", [17, 63, 64, 65, 16384, 16385, 32769, 40960, 40961, 98304, 98305])
+def test_small_batch_tile_heights(dev, V, K):
+    """Batches of up to 64 rows: on both sides of each line between the tile
+    heights of 64, 128 and 256, with a row or a remainder in the last tile."""
+    for N, H in ((1, 72), (64, 1032)):
+        check_topk(*exact_inputs(N, H, V, seed=N + V + H + K, dev=dev), min(K, V),
+                   f"fused N={N} H={H} V={V} K={K}")
