@@ -479,8 +479,12 @@ __global__ __launch_bounds__(C::NT) void proj_topk_part(
 // 4096 x 128256 168 / 177; but on the same w again 64 x 2048 x 68000, 279 MB,
 // 84 / 68, and with more strips, which share w in L2, 768 x 4096 x 128256 750 /
 // 730).  The logits' 256 x 256 tiles gain nothing (256 x 4096 x 128256 345 / 345).
-static bool w_once(int64_t N, int64_t H, int64_t V, int64_t rows) {
-    return N <= rows && V * H * 2 >= ((int64_t)384 << 20);
+// Only where a tile row's 128 bytes of a step are a whole cache line: a line
+// that two steps share would be fetched twice (64 x 4080 x 60000 logits 148 /
+// 117, top-5 156 / 125).
+static bool w_once(const void* w, int64_t N, int64_t H, int64_t V, int64_t rows) {
+    return N <= rows && V * H * 2 >= ((int64_t)384 << 20) && H % PJ_BK == 0 &&
+           reinterpret_cast<uintptr_t>(w) % (PJ_BK * 2) == 0;
 }
 
 template <class C, bool PP, int WA>
@@ -501,7 +505,7 @@ hipError_t launch_proj_logits(const void* h, const void* w, float* out, int64_t 
                               int64_t V, int cus, hipStream_t st) {
     const int64_t big = ((N + PjBig::TX - 1) / PjBig::TX) * ((V + PjBig::TY - 1) / PjBig::TY);
     if (big >= 2 * (int64_t)cus) return launch_logits_t<PjBig, true, 0>(h, w, out, N, H, V, st);
-    if (w_once(N, H, V, PjSmall::TX))
+    if (w_once(w, N, H, V, PjSmall::TX))
         return launch_logits_t<PjSmall, false, PJ_ONCE>(h, w, out, N, H, V, st);
     return launch_logits_t<PjSmall, false, 0>(h, w, out, N, H, V, st);
 }
@@ -565,7 +569,7 @@ hipError_t launch_proj_topk(const void* h, const void* w, float* vals, int32_t* 
             h, w, pkeys, pmd, N, H, V, K, S, tiles, st);
     };
     auto run = [&](auto cfg, auto kc, auto pp) {
-        if (w_once(N, H, V, decltype(cfg)::TY))
+        if (w_once(w, N, H, V, decltype(cfg)::TY))
             part_of(cfg, kc, pp, std::integral_constant<int, PJ_ONCE>{});
         else
             part_of(cfg, kc, pp, std::integral_constant<int, 0>{});

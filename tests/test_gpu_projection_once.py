@@ -10,13 +10,16 @@ from parity import RTOL
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,K", [(1, 5), (64, 16), (100, 5), (128, 16), (200, 8), (256, 12)])
-def test_large_vocabulary(N, K):
-    H, V = 4096, 49153  # 384 MiB + 8 KiB: one row into the last tile
+@pytest.mark.parametrize("N,K,H,V", [
+    (1, 5, 4096, 49153), (64, 16, 4096, 49153),  # 384 MiB and one row of 8 KiB
+    (100, 5, 4096, 49153), (128, 16, 4096, 49153), (200, 8, 4096, 49153), (256, 12, 4096, 49153),
+    (64, 5, 4088, 49300), (64, 12, 4104, 49300),  # rows of part lines: the default policy
+])
+def test_large_vocabulary(N, K, H, V):
     g = torch.Generator(device="cuda").manual_seed(N)
     h = torch.randn(N, H, generator=g, device="cuda").bfloat16()
     w = (torch.randn(V, H, generator=g, device="cuda") / 64).bfloat16()
-    print(f"N={N} K={K}", flush=True)
+    print(f"N={N} K={K} H={H} V={V}", flush=True)
     out = osm.proj(h, w)
     cut = 24576
     parts = torch.cat([osm.proj(h, w[:cut]), osm.proj(h, w[cut:])], dim=1)
