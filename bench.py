@@ -547,7 +547,7 @@ def kernel_stats_summary(d: str, out_name: str, command: str):
 
 # The kernels of one bench step (name prefixes as the profiler reports them):
 # the online softmax of the 4000 x 32000 binary32 batch and its fused top-5.
-STEP_KERNELS = ("osm::softmax_rows<float, 2, 1024, 1024,", "osm::topk_fused<float, 1, 5, 0,")
+STEP_KERNELS = ("osm::softmax_rows<float, 2, 1024, 1024,", "osm::topk_held<float, 8, 16, 0,")
 
 # Core counters of the fused top-k and of the projection kernels: a kernel
 # trace and two counter passes per probe (each pass its own process, within
@@ -624,7 +624,7 @@ def counters_summary(kind: str, d: str):
         L += ["# Fused softmax + top-k: kernel time and core counters", "",
               "Commands (repository root, GPU host; each counter pass its own process):", "",
               "```", *cmds, "```", "", f"Kernel sources hash: `{kernel_source_sha()}`", "",
-              "Three calls per case, in the order below (one wavefront per row). VALU busy =",
+              "Three calls per case, in the order below. VALU busy =",
               "SQ_ACTIVE_INST_VALU / (4 SIMDs x SQ_BUSY_CU_CYCLES); waiting = SQ_WAIT_ANY / "
               "SQ_WAVE_CYCLES",
               "(wave cycles spent on a dependency, mostly `s_waitcnt` for loads); VALU and LDS "
@@ -633,7 +633,7 @@ def counters_summary(kind: str, d: str):
               "(median of the three).", "",
               "| case | K | kernel | us | GB/s | VALU busy | waiting | VALU instr / element | "
               "LDS instr / element |", "|---|---|---|---|---|---|---|---|---|"]
-        tk = [t for n, t in trace if n.startswith("osm::topk_fused")]
+        tk = [t for n, t in trace if n.startswith(("osm::topk_held", "osm::topk_fused"))]
         for ci, (case, N, V, es, K) in enumerate(TOPK_PROBE_CASES):
             us = median(tk[3 * ci:3 * ci + 3]) / 1e3
             rows = [merged(3 * ci + j) for j in range(3)]
