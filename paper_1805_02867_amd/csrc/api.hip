@@ -226,8 +226,25 @@ Plan choose(int64_t N, int64_t V, int dtype, int cus) {
     if (nv <= 16) return {OSM_KERNEL_ROWS, 4};
     if (nv <= 32) return {OSM_KERNEL_ROWS, 8};
     if (nv <= 64) return {OSM_KERNEL_ROWS, 16};
-    if (nv <= 128) return {OSM_KERNEL_ROWS, 32};
-    if (nv <= 1024) return {OSM_KERNEL_ROWS, 64};
+    // The longer of them with few rows, which leave most of the chip idle, take
+    // a workgroup each (us, a wavefront a row -> this; binary32 64 x 1500 4.06 ->
+    // 3.30, 400 x 1000 3.64 -> 3.37, 200 x 4096 6.5 -> 3.4, but 400 x 600 3.04 ->
+    // 3.20; bfloat16 64 x 2000 4.4 -> 3.0, 200 x 8192 8.2 -> 3.8), then two
+    // wavefronts (binary32 800 x 4096 6.9 -> 4.9, but 1024 x 2000 5.08 -> 5.14).
+    // Larger batches keep a wavefront, but for bfloat16 rows of 513 to 768
+    // vectors (4000 x 5000 18.8 -> 15.6, 32768 x 6200 178 -> 153; 3000 x 2400
+    // 6.9 -> 7.7).
+    const int64_t c = cus;
+    if (nv <= 128) {  // bfloat16: 200 x 1000 4.4 -> 3.0, but 512 x 600 3.40 -> 3.55
+        if (dtype != OSM_F32 && nv > 96 && N <= 2 * c) return {OSM_KERNEL_ROWS, 128};
+        return {OSM_KERNEL_ROWS, 32};
+    }
+    if (nv <= 1024) {
+        if (N <= (nv > 200 ? 2 * c : nv > 160 ? c : 0)) return {OSM_KERNEL_ROWS, 256};
+        if (nv > 512 && N <= 4 * c && N > 2 * c) return {OSM_KERNEL_ROWS, 128};
+        if (dtype != OSM_F32 && nv > 512 && nv <= 768 && N >= 8 * c) return {OSM_KERNEL_ROWS, 128};
+        return {OSM_KERNEL_ROWS, 64};
+    }
     // Long rows but too few of them to fill the chip: split each row, into
     // about four chunks per CU in all, six for the smallest batches (at 10
     // rows of 10^6: 19.5 us with six against 22.5 with four; at 64 or 256

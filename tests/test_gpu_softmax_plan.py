@@ -34,3 +34,26 @@ def test_plan_line(N, V, dtype, kernel):
         pick = [0, 1, N // 2, N - 1]
         assert_softmax_close(to_host(y[pick]), oracle.softmax(to_host(x[pick]), host_dtype(x)),
                              f"{N}x{V} {dtype} {mode}")
+
+
+@pytest.mark.parametrize("N,V,dtype,lanes", [
+    (512, 768, "bf16", 32), (512, 769, "bf16", 128), (513, 1024, "bf16", 32), (3, 512, "f32", 32),
+    (256, 640, "f32", 64), (256, 641, "f32", 256), (257, 800, "f32", 64), (512, 801, "f32", 256),
+    (513, 2048, "f32", 64), (512, 4096, "f32", 256), (513, 2049, "f32", 128),
+    (1024, 4093, "f32", 128), (1025, 4096, "f32", 64), (2, 1281, "bf16", 256),
+    (1024, 8192, "bf16", 128), (2047, 4097, "bf16", 64), (2048, 4097, "bf16", 128),
+    (2048, 6144, "bf16", 128), (2048, 6145, "bf16", 64),
+])
+def test_lanes_line(N, V, dtype, lanes):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the batch sizes stand for 256 CUs")
+    x = synth.logits(N, V, sigma=3.0, seed=V + N, dtype=dtype, device="cuda")
+    x[0, 1:] = float("-inf")
+    x[1] = 0.5
+    for mode in ("naive", "safe", "online"):
+        print(f"{N}x{V} {dtype} {mode}", flush=True)
+        assert osm.plan(N, V, dtype=x.dtype, mode=mode) == (R, lanes)
+        y = osm.softmax_fwd(x, mode=mode)
+        pick = [0, 1, N // 2, N - 1]
+        assert_softmax_close(to_host(y[pick]), oracle.softmax(to_host(x[pick]), host_dtype(x)),
+                             f"{N}x{V} {dtype} {mode}")
