@@ -232,7 +232,7 @@ Plan choose(int64_t N, int64_t V, int dtype, int cus) {
     // 3.20; bfloat16 64 x 2000 4.4 -> 3.0, 200 x 8192 8.2 -> 3.8), then two
     // wavefronts (binary32 800 x 4096 6.9 -> 4.9, but 1024 x 2000 5.08 -> 5.14).
     // Larger batches keep a wavefront, but for bfloat16 rows of 513 to 768
-    // vectors (4000 x 5000 18.8 -> 15.6, 32768 x 6200 178 -> 153; 3000 x 2400
+    // vectors (4000 x 5000 18.8 -> 15.6, 32768 x 5000 139 -> 115; 3000 x 2400
     // 6.9 -> 7.7).
     const int64_t c = cus;
     if (nv <= 128) {  // bfloat16: 200 x 1000 4.4 -> 3.0, but 512 x 600 3.40 -> 3.55
