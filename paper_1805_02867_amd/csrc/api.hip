@@ -657,7 +657,7 @@ int osm_topk_plan(int64_t N, int64_t V, int dtype, int K, int* kernel, int64_t* 
     if (K < 1 || K > OSM_TOPK_KMAX || (int64_t)K > V) return OSM_EINVAL;
     if (!kernel || !param) return OSM_EINVAL;
     DeviceState* ds = device_state(nullptr);
-    Plan p = choose_topk(N, V, dtype, K, ds ? ds->cus : 256);
+    Plan p = choose_topk(N > 0 ? N : 1, V, dtype, K, ds ? ds->cus : 256);
     *kernel = p.kernel;
     *param = p.param;
     return OSM_OK;
@@ -710,7 +710,7 @@ int osm_plan(int64_t N, int64_t V, int dtype, int mode, int* kernel, int64_t* pa
         return OSM_OK;
     }
     DeviceState* ds = device_state(nullptr);
-    Plan p = choose(N, V, dtype, ds ? ds->cus : 256);
+    Plan p = choose(N > 0 ? N : 1, V, dtype, ds ? ds->cus : 256);
     *kernel = p.kernel;
     *param = p.param;
     return OSM_OK;

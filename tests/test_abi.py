@@ -241,6 +241,16 @@ def test_topk_plan_rejects_bad_arguments():
     assert osm.lib().osm_topk_plan(4, 10, 0, 5, None, ctypes.byref(p)) == osm.EINVAL
 
 
+@pytest.mark.parametrize("V", [1000, 20481, 1_000_000])
+def test_plans_of_an_empty_batch(V):
+    """N = 0 is a valid size: the planners answer as for one row."""
+    for dt in (osm.F32, osm.BF16):
+        for mode in (osm.NAIVE, osm.SAFE, osm.ONLINE):
+            assert osm.plan(0, V, dtype=dt, mode=mode) == osm.plan(1, V, dtype=dt, mode=mode)
+        for K in (1, 64):
+            assert osm.topk_plan(0, V, K, dtype=dt) == osm.topk_plan(1, V, K, dtype=dt)
+
+
 def test_python_binding_refuses_cpu_tensors():
     import torch
     with pytest.raises(ValueError):
