@@ -249,7 +249,8 @@ def topk(x: torch.Tensor, K: int, vals: torch.Tensor | None = None,
 def stream_release(stream=None) -> None:
     """Frees the scratch the library keeps for `stream` (``osm_stream_release``),
     in stream order; call before destroying a stream that used the library."""
-    torch.cuda.init()  # the current stream may be asked for before any tensor was made
+    if stream is None:
+        torch.cuda.init()  # the current stream may be asked for before any tensor was made
     rc = lib().osm_stream_release(_stream(stream))
     if rc != OK:
         raise OsmError(rc, "osm_stream_release")

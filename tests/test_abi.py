@@ -261,6 +261,17 @@ def test_python_binding_refuses_cpu_tensors():
         osm.topk(torch.zeros(2, 3), 1)
 
 
+def test_stream_release_of_a_given_stream_asks_the_library_only():
+    """A stream given as a handle needs no device of torch's: without a GPU
+    the library's own status is what the caller sees."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("what a machine without a GPU answers")
+    with pytest.raises(osm.OsmError) as e:
+        osm.stream_release(0x1000)
+    assert e.value.status == osm.EHIP
+
+
 @pytest.mark.parametrize("args", [
     (2, H_, W_, 1024),        # unknown op
     (0, H_, W_, -16),         # negative size
