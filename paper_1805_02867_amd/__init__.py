@@ -88,12 +88,20 @@ def status_string(status: int) -> str:
     return lib().osm_status_string(int(status)).decode()
 
 
+# torch's current device and stream handle, asked for directly (None where a
+# torch release has no such entry)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if _device else None
+
+
 def _stream(stream) -> int:
     """The HIP stream handle of `stream`, or of torch's current stream.  The
     handle is asked for directly: torch.cuda.current_stream() builds a stream
     object for it, 2.8 us of the ~8.5 a small call took (0.2 this way)."""
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)

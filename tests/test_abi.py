@@ -261,6 +261,19 @@ def test_python_binding_refuses_cpu_tensors():
         osm.topk(torch.zeros(2, 3), 1)
 
 
+def test_current_stream_without_the_direct_entry(monkeypatch):
+    """Where torch has no direct entry for the current stream's handle, its
+    public stream object gives it."""
+    import types
+
+    import torch
+    monkeypatch.setattr(osm, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    assert osm._stream(None) == 0x1230
+    assert osm._stream(0x4560) == 0x4560
+
+
 def test_stream_release_of_a_given_stream_asks_the_library_only():
     """A stream given as a handle needs no device of torch's: without a GPU
     the library's own status is what the caller sees."""
