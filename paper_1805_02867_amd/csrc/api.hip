@@ -11,6 +11,7 @@
 namespace {
 
 constexpr int64_t kMaxDim = 2147483647;  // 2^31 - 1
+constexpr int64_t kMaxThreads = 4294967295;  // of one launch, workgroups times their size
 constexpr int kMaxDevices = 64;
 
 size_t elem_size(int dtype) { return dtype == OSM_BF16 ? 2 : 4; }
@@ -413,11 +414,14 @@ Plan choose_topk_stream(int64_t N, int64_t V, int K, int cus, int64_t min_chunk 
 //    against 8.0; top-50 9.9 against 9.3);
 //  * longer rows are streamed or split, the chunks with at least 2048 vectors
 //    (16 x 128256 bfloat16 top-5: 9.4 in 8 chunks, 12.4 in 31), or 1024 for a
-//    few rows (1 x 128256 bfloat16 top-5: 8.2 in 7 chunks, 7.1 in 31).
+//    few rows (1 x 128256 bfloat16 top-5: 8.2 in 7 chunks, 7.1 in 31);
+//  * a batch of so many rows that a workgroup each would pass what one launch
+//    takes (2^24 rows and more: 275 GB of the shortest such rows) keeps a
+//    wavefront a row.
 Plan choose_topk(int64_t N, int64_t V, int dtype, int K, int cus) {
     const int64_t E = elems_per_vec(dtype), nv = V / E;
     const bool many = N >= 4 * (int64_t)cus;
-    if (V <= 1536 || (many && nv <= 1024)) return {OSM_KERNEL_ROWS, 64};
+    if (V <= 1536 || (many && nv <= 1024) || N * 256 > kMaxThreads) return {OSM_KERNEL_ROWS, 64};
     if (nv <= 4096) return {OSM_KERNEL_ROWS, 256};
     if (nv <= 8192 && (many ? dtype == OSM_F32 || N < 8 * (int64_t)cus : N >= 16 || K > 8))
         return {OSM_KERNEL_ROWS, 256};

@@ -251,6 +251,14 @@ def test_plans_of_an_empty_batch(V):
             assert osm.topk_plan(0, V, K, dtype=dt) == osm.topk_plan(1, V, K, dtype=dt)
 
 
+@pytest.mark.parametrize("dtype,V", [(osm.F32, 4100), (osm.BF16, 8200)])
+def test_topk_plan_fits_one_launch(dtype, V):
+    """A launch takes fewer than 2^32 threads: the rows of the largest batches
+    (275 GB) take a wavefront each instead of a workgroup of four."""
+    assert osm.topk_plan((1 << 24) - 1, V, 5, dtype=dtype) == (osm.KERNEL_ROWS, 256)
+    assert osm.topk_plan(1 << 24, V, 5, dtype=dtype) == (osm.KERNEL_ROWS, 64)
+
+
 def test_python_binding_refuses_cpu_tensors():
     import torch
     with pytest.raises(ValueError):
