@@ -48,6 +48,19 @@ constexpr int TH_CUT = 128;   // a longer list is cut back to its K largest
 __device__ __forceinline__ uint32_t order_word(float x) { return (uint32_t)(make_key(x, 0u) >> 32); }
 constexpr uint32_t kOrderNegInf = 0x007FFFFFu;  // image of -infinity
 
+// A condition that few rows meet: its code goes behind the kernel's (a short
+// row's time is mostly the first pass through the code it runs).
+__device__ __forceinline__ bool rare(bool c) { return __builtin_expect(c, 0); }
+
+struct KthBound {
+    uint32_t lo;  // the bound
+    // Many more words than K reach lo, for [lo, up) holds one value only, which
+    // the K-th largest word has: a row of ties, as it seems.
+    bool tied;
+    uint32_t up;
+};
+constexpr int TH_TIED = 16;  // how many more, past the K + K / 4 + 1 of an ordinary bound
+
 // A word that at least K of the wavefront's 64 * G words reach (K <= 64 G;
 // kOrderNegInf if fewer than K are above it), given `hi`, the largest of them.
 // The words' distance below hi is bracketed in powers of four from one binade
@@ -58,7 +71,7 @@ constexpr uint32_t kOrderNegInf = 0x007FFFFFu;  // image of -infinity
 // twelve.  (Every lane of the wavefront takes part; the result is the same in
 // all.)
 template <int G, uint32_t GRAN>
-__device__ __forceinline__ uint32_t kth_bound(const uint32_t (&m)[G], uint32_t hi, int K) {
+__device__ __forceinline__ KthBound kth_bound(const uint32_t (&m)[G], uint32_t hi, int K) {
     const int most = K + (K >> 2) + 1;
     auto count = [&](uint32_t c) {
         int n = 0;
@@ -66,18 +79,19 @@ __device__ __forceinline__ uint32_t kth_bound(const uint32_t (&m)[G], uint32_t h
         for (int g = 0; g < G; ++g) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(m[g] >= c));
         return n;
     };
-    if (hi <= kOrderNegInf) return kOrderNegInf;
-    if (count(hi) >= K) return hi;
+    const KthBound none = {kOrderNegInf, true, kOrderNegInf + 1};
+    if (hi <= kOrderNegInf) return none;
+    int n = count(hi);
+    if (n >= K) return {hi, n > most + TH_TIED, hi + 1};
     // n words reach lo, at least K; fewer than K reach up
     uint32_t lo, up = hi, step = 1u << 23;
-    int n;
 #pragma unroll 1
     for (;;) {
         const bool last = step >= hi - kOrderNegInf;
         lo = last ? kOrderNegInf + 1 : hi - step;
         n = count(lo);
         if (n >= K) break;
-        if (last) return kOrderNegInf;
+        if (last) return none;
         up = lo;
         step = step < (1u << 30) ? step << 2 : 0xFFFFFFFFu;
     }
@@ -92,13 +106,22 @@ __device__ __forceinline__ uint32_t kth_bound(const uint32_t (&m)[G], uint32_t h
             up = c;
         }
     }
-    return lo;
+    return {lo, n > most + TH_TIED, up};
 }
 
 // The wavefront's largest value, as a scalar.
 __device__ __forceinline__ float wave_max_f(float v) {
     return __uint_as_float(
         (uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(group_max<64>(v))));
+}
+
+// The largest of the wavefront's words, as a scalar.
+template <int G>
+__device__ __forceinline__ uint32_t wave_hi(const uint32_t (&m)[G]) {
+    uint32_t h = m[0];
+#pragma unroll
+    for (int g = 1; g < G; ++g) h = m[g] > h ? m[g] : h;
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(h));
 }
 
 // Sort of the wavefront's keys (lane 0 ends with the largest) when only the
@@ -208,22 +231,14 @@ struct HeldSmem {
     uint32_t gmax[W == 1 ? 1 : 256];  // images of 256 groups' maxima
     MD wmd[NW];
     int cnt[NW];
+    int tie[NW];
 };
-
-// The largest of the wavefront's words, as a scalar.
-template <int G>
-__device__ __forceinline__ uint32_t wave_hi(const uint32_t (&m)[G]) {
-    uint32_t h = m[0];
-#pragma unroll
-    for (int g = 1; g < G; ++g) h = m[g] > h ? m[g] : h;
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max_u32(h));
-}
 
 // A word that at least K of a workgroup's elements reach, from the maxima `m`
 // of its lanes' elements: up to 256 groups (of one lane, or W / 4) go through
 // LDS, and every wavefront runs the same search.  (One barrier.)
 template <int W, uint32_t GRAN, class Smem>
-__device__ __forceinline__ uint32_t team_bound(Smem& sm, uint32_t m, int K) {
+__device__ __forceinline__ KthBound team_bound(Smem& sm, uint32_t m, int K) {
     constexpr int GL = W > 4 ? W / 4 : 1, G = W > 4 ? 4 : W;
     const int lane = threadIdx.x & 63;
     if constexpr (GL >= 2) {
@@ -293,7 +308,7 @@ __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* p
                 const uint32_t h = (uint32_t)(k[i] >> 32);
                 g[i % 4] = h > g[i % 4] ? h : g[i % 4];
             }
-            t = kth_bound<4, GRAN>(g, wave_hi(g), K);
+            t = kth_bound<4, GRAN>(g, wave_hi(g), K).lo;
         } else {
             uint32_t m = 0;
 #pragma unroll
@@ -301,7 +316,7 @@ __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* p
                 const uint32_t h = (uint32_t)(k[i] >> 32);
                 m = h > m ? h : m;
             }
-            t = team_bound<W, GRAN>(sm, m, K);
+            t = team_bound<W, GRAN>(sm, m, K).lo;
         }
         uint32_t hm = 0;
 #pragma unroll
@@ -313,7 +328,7 @@ __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* p
 #pragma unroll
             for (int i = 1; i < R; ++i) q = s == i ? k[i] : q;
             hl.offer(hm != 0, q);
-            if (hl.n > TH_CUT) hl.cut();
+            if (rare(hl.n > TH_CUT)) hl.cut();
             hm &= hm - 1;
         }
     }
@@ -391,12 +406,12 @@ __device__ __forceinline__ float held_vmax(u32x4 q) {
 
 // Offers the candidates of a block of R vectors a lane (lane's vectors v0,
 // v0 + TR, ...; bit i of hm: vector i holds an element of at least `th`), and
-// of the lane's head or tail element (bit R).  Per round each lane takes one
+// the lane's head or tail element (bit R).  Per round each lane takes one
 // vector, then its candidates one at a time.
 template <typename T, int R, int TR>
 __device__ __forceinline__ void held_offer(HeldList& hl, const HeldSpan<T>& sp,
                                            const u32x4 (&buf)[R], int v0, uint32_t hm, float th,
-                                           float ex, int ei) {
+                                           float ex) {
     constexpr int E = Vec<T>::N;
 #pragma unroll 1
     while (__builtin_amdgcn_ballot_w64(hm != 0) != 0) {
@@ -417,12 +432,12 @@ __device__ __forceinline__ void held_offer(HeldList& hl, const HeldSpan<T>& sp,
         widen<T>(q, xv);
         if (s == R) {
             xv[0] = ex;
-            i0 = sp.base + (uint32_t)ei;
+            i0 = sp.base + (uint32_t)sp.extra(v0);
         }
         uint32_t em = 0;  // candidates among the vector's elements
 #pragma unroll
         for (int e = 0; e < E; ++e) em |= (uint32_t)(xv[e] >= th) << e;
-        if (s == R) em &= 1u;
+        if (s == R) em = 1u;
         if (hm == 0) em = 0;
 #pragma unroll 1
         while (__builtin_amdgcn_ballot_w64(em != 0) != 0) {
@@ -431,11 +446,63 @@ __device__ __forceinline__ void held_offer(HeldList& hl, const HeldSpan<T>& sp,
 #pragma unroll
             for (int k = 1; k < E; ++k) v = e == k ? xv[k] : v;
             hl.offer(em != 0, make_key(v, i0 + (uint32_t)e));
-            if (hl.n > TH_CUT) hl.cut();
+            if (rare(hl.n > TH_CUT)) hl.cut();
             em &= em - 1;
         }
         hm &= hm - 1;
     }
+}
+
+// Rows of ties: the elements of one value, the only one in [lo, up), when the
+// team's first vectors (one a lane, q) hold at least K of them.  Those are the
+// K of lowest index: each wavefront appends its own, and the rest of the ties
+// is never looked at.  False: they hold fewer, nothing was appended.  (The list
+// is empty, in: the lane has such a vector; the team enters together.)
+// Equal elements, 4000 x 32000 binary32 top-5: 239 us looked at one by one, with
+// a selection after every 64 of them; 77 us in this way, as other rows.
+template <typename T, int W>
+__device__ __forceinline__ bool held_ties(HeldSmem<W>& sm, HeldList& hl, u32x4 q, bool in,
+                                          uint32_t idx0, float lo, float up) {
+    constexpr int E = Vec<T>::N;
+    uint32_t tie = 0;       // bit e: element e is one
+    int at = 0, total = 0;  // ties in the lanes before this one, and in all
+    float xv[E];
+    widen<T>(q, xv);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const bool is = in && xv[e] >= lo && !(xv[e] >= up);
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(is);
+        tie |= (uint32_t)is << e;
+        at += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        total += __builtin_popcountll(mask);
+    }
+    int room = hl.K, all = total;
+    if constexpr (W > 1) {
+        const int lane = threadIdx.x & 63;
+        const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (lane == 0) sm.tie[wv] = total;
+        __syncthreads();
+        const int counts = sm.tie[lane % W];
+        all = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int c = __builtin_amdgcn_readlane(counts, w);
+            all += c;
+            room -= w < wv ? c : 0;
+        }
+    }
+    if (all < hl.K) return false;
+    opaque(q);
+    widen<T>(q, xv);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int is = tie >> e & 1;
+        if (is && at < room) hl.keys[at] = make_key(xv[e], idx0 + (uint32_t)e);
+        at += is;
+    }
+    hl.n = room < 0 ? 0 : total < room ? total : room;
+    return true;
 }
 
 // The end of a team's work: its lists' K largest keys and its pair, written as
@@ -515,11 +582,25 @@ __device__ __forceinline__ void held_end(HeldSmem<W>& sm, HeldList& hl, MD md,
     }
 }
 
+// Wavefronts per SIMD asked of the compiler: as many as R vectors a lane leave
+// registers for (64, 80 or 96 of them), without which it takes a few more.
+// (Five, with workgroups of two a SIMD, let the next workgroup's loads start
+// under the first wavefront's end of the one before: 511 x 50257 binary32 top-5,
+// split, 25.5 us, against 27.6 with four.)
+template <typename T, int W, int R, bool PART>
+constexpr int held_waves() {
+    const bool more = Vec<T>::N == 8 && (W == 8 || PART);  // bfloat16 widens to twice as many
+    return R <= 6    ? (PART ? 7 : 8)
+           : R <= 8  ? (more ? 6 : PART ? 7 : 8)
+           : R <= 12 ? (more || PART ? 5 : 6)
+                     : (more && W == 4 ? 4 : 5);
+}
+
 // Rows (PART = false: vr is a row, segs = 1) or chunks of rows (PART = true:
 // chunk vr % segs of `seg` elements of row vr / segs) of at most 64 W R whole
 // 16-byte vectors, W wavefronts each, held in registers.
 template <typename T, int W, int R, int VAR, bool PART>
-__global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_held(
+__global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W, (held_waves<T, W, R, PART>())) void topk_held(
     const T* __restrict__ x, float* __restrict__ vals, int32_t* __restrict__ idx, uint64_t* pkeys,
     MD* pmd, uint32_t* ctr, int64_t N, int64_t V, int K, int64_t seg, int64_t segs) {
     static_assert(!PART || W > 1, "chunks take a workgroup each");
@@ -549,8 +630,7 @@ __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_held(
 #pragma unroll
         for (int i = 0; i < R; ++i) buf[i] = u32x4{0, 0, 0, 0};
     }
-    const int ei = sp.extra(tr);
-    const float ex = tr < sp.ne ? load1(sp.xr + ei) : ninf;
+    const float ex = tr < sp.ne ? load1(sp.xr + sp.extra(tr)) : ninf;
 
     // 1. maxima by vector, and the wavefront's
     float vm[R];
@@ -581,7 +661,7 @@ __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_held(
     }
     // 2. the threshold: W = 1 from the maxima of up to four groups of each
     //    lane's elements (elements of one vector when it holds no more)
-    uint32_t t;
+    KthBound b;
     if constexpr (W == 1) {
         constexpr int G = R == 1 ? 2 : R < 4 ? R : 4;
         float gm[G];
@@ -600,20 +680,34 @@ __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_held(
         uint32_t g[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) g[i] = order_word(gm[i]);
-        t = kth_bound<G, GRAN>(g, order_word(wm), K);
+        b = kth_bound<G, GRAN>(g, order_word(wm), K);
     } else {
-        t = team_bound<W, GRAN>(sm, order_word(lm), K);
+        b = team_bound<W, GRAN>(sm, order_word(lm), K);
     }
-    const float th = key_value((uint64_t)t << 32);
-    // 3. the candidates
+    // 3. the candidates: elements at or above the bound
     HeldList hl{sm.list[wv], K, 0, 0ull};
+    float th = key_value((uint64_t)b.lo << 32);
     uint32_t hm = (uint32_t)(tr < sp.ne && ex >= th) << R;
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         opaque(buf[i]);
         hm |= (uint32_t)(tr + i * TR < nvec && vm[i] >= th) << i;
     }
-    held_offer<T, R, TR>(hl, sp, buf, tr, hm, th, ex, ei);
+    if (rare(b.tied && nvec >= K)) {  // (not for want of elements)
+        const float up = key_value((uint64_t)b.up << 32);
+        if (held_ties<T, W>(sm, hl, buf[0], tr < nvec, sp.index(tr), th, up)) {
+            // the ties are settled: what is left are elements above them (the
+            // maxima are found again, so that they need not be kept until here)
+            th = up;
+            hm &= 1u << R;
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                opaque(buf[i]);
+                hm |= (uint32_t)(tr + i * TR < nvec && held_vmax<T, VAR>(buf[i]) >= th) << i;
+            }
+        }
+    }
+    held_offer<T, R, TR>(hl, sp, buf, tr, hm, th, ex);
     // 4. the K largest, in order
     held_end<W, VAR, PART, GRAN>(sm, hl, md, vals, idx, pkeys, pmd, ctr, row, vr, segs, K);
 }
