@@ -285,6 +285,7 @@ __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* p
     }
     HeldList hl{sm.list[slot], K, 0, 0ull};
     uint64_t top = 0;  // W = 1, K = 1: the largest key, without threshold or list
+    uint32_t t = 0;    // a word that at least K of the first batch's keys reach
 #pragma unroll 1
     for (int64_t b = 0; b < n; b += TR * R) {
         uint64_t k[R];
@@ -296,10 +297,8 @@ __device__ __forceinline__ bool held_merge(Smem& sm, int slot, const uint64_t* p
             for (int i = 0; i < R; ++i) top = k[i] > top ? k[i] : top;
             continue;
         }
-        uint32_t t = 0;
         if (b > 0) {
-            // the list's K-th key filters the later batches
-            if (hl.tau == 0) hl.cut();
+            // the first batch's bound holds for the later ones
         } else if constexpr (W == 1) {
             static_assert(R % 4 == 0, "four groups a lane");
             uint32_t g[4] = {0, 0, 0, 0};
