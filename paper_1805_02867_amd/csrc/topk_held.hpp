@@ -145,6 +145,34 @@ __device__ __forceinline__ uint64_t merge_sorted(uint64_t a, uint64_t b) {
     return bitonic_merge_desc(a > b ? a : b);
 }
 
+// Of up to 192 keys (three a lane, 0: none), those that can be among the K
+// largest, written to `out`: all keys whose value reaches a bound that at least
+// K of them reach, K + K / 4 + 1 or fewer but for ties.  Returns how many; lo:
+// the bound.  (A few counts, where sorting 192 keys takes three networks of 21
+// dependent exchanges and three merges.  Rows whose largest elements lie side
+// by side, so that a lane's group holds many, need it: logits that fall with
+// the index, top-50, 4000 x 32000 binary32 108 -> 100 us, 4000 x 1000 13.1 ->
+// 11.5, 2000 x 60000 bfloat16 69 -> 62; in any order 81.5, 9.0 and 47.8.)
+__device__ __forceinline__ int thin_keys(const uint64_t (&k)[3], int K, uint64_t* out,
+                                         uint32_t* lo) {
+    uint32_t g[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) g[j] = (uint32_t)(k[j] >> 32);
+    const uint32_t b = kth_bound<3, 1>(g, wave_hi(g), K).lo;
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const bool p = g[j] >= b;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(p);
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        if (p) out[n + below] = k[j];
+        n += __builtin_popcountll(mask);
+    }
+    *lo = b;
+    return n;
+}
+
 // A wavefront's list of candidate keys.
 struct HeldList {
     uint64_t* keys;  // TH_LIST slots of LDS
@@ -162,9 +190,19 @@ struct HeldList {
         if (p) keys[n + below] = key;
         n += __builtin_popcountll(mask);
     }
-    // The K largest keys stay; fewer than K set no filter.  (Every lane takes part.)
+    // More than TH_CUT keys: those that can be among the K largest stay, or the
+    // K largest themselves where ties leave more of them.  (Every lane takes part.)
     __device__ __forceinline__ void cut() {
         const int lane = __lane_id();
+        uint64_t k[3];
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < 3; ++j) k[j] = lane + 64 * j < n ? keys[lane + 64 * j] : 0ull;
+        uint32_t lo;
+        n = thin_keys(k, K, keys, &lo);
+        const uint64_t t = ((uint64_t)lo << 32) - 1;
+        tau = t > tau ? t : tau;
+        if (n <= TH_CUT) return;
         uint64_t cur = 0;
         wave_sync();
 #pragma unroll 1
@@ -172,7 +210,6 @@ struct HeldList {
             cur = merge_sorted(cur, sort_desc(b + lane < n ? keys[b + lane] : 0ull));
         wave_sync();
         if (lane < K) keys[lane] = cur;
-        if (n < K) return;
         n = K;
         tau = read_lane_key(cur, K - 1);
     }
@@ -182,26 +219,40 @@ struct HeldList {
 // the calling wavefront returns the k-th largest key (0: none).  Batches of 64
 // keys of the lists' concatenation; one batch when they hold no more.
 template <int W>
-__device__ __forceinline__ uint64_t held_finish(const uint64_t (*lists)[TH_LIST], const int* cnt,
+__device__ __forceinline__ uint64_t held_finish(uint64_t (*lists)[TH_LIST], const int* cnt,
                                                 int K) {
     const int lane = __lane_id();
     int total = 0;
 #pragma unroll
     for (int w = 0; w < W; ++w) total += cnt[w];
     total = __builtin_amdgcn_readfirstlane(total);
-    uint64_t cur = 0;
-#pragma unroll 1
-    for (int b = 0; b < total; b += 64) {
-        int i = b + lane, w = 0;
+    // key i of the concatenation
+    auto at = [&](int i) {
+        int w = 0, j = i;
 #pragma unroll
         for (int u = 0; u < W - 1; ++u) {
             const int c = cnt[u];
-            const bool past = w == u && i >= c;
-            i = past ? i - c : i;
+            const bool past = w == u && j >= c;
+            j = past ? j - c : j;
             w = past ? u + 1 : w;
         }
-        uint64_t q = b + lane < total ? lists[w][i] : 0ull;
-        q = sort_first(q, total - b);
+        return i < total ? lists[w][j] : 0ull;
+    };
+    if (W > 1 && rare(total > 64 && total <= TH_LIST)) {  // thinned out ahead of the sort
+        const uint64_t k[3] = {at(lane), at(lane + 64), at(lane + 128)};
+        uint32_t lo;
+        const int n = thin_keys(k, K, lists[0], &lo);
+        wave_sync();
+        uint64_t cur = sort_desc(lane < n ? lists[0][lane] : 0ull);
+#pragma unroll 1
+        for (int b = 64; b < n; b += 64)
+            cur = merge_sorted(cur, sort_desc(b + lane < n ? lists[0][b + lane] : 0ull));
+        return lane < K ? cur : 0ull;
+    }
+    uint64_t cur = 0;
+#pragma unroll 1
+    for (int b = 0; b < total; b += 64) {
+        const uint64_t q = sort_first(at(b + lane), total - b);
         if (b == 0) cur = q;
         else cur = merge_sorted(cur, q);
     }
@@ -445,7 +496,10 @@ __device__ __forceinline__ void held_offer(HeldList& hl, const HeldSpan<T>& sp,
 #pragma unroll
             for (int k = 1; k < E; ++k) v = e == k ? xv[k] : v;
             hl.offer(em != 0, make_key(v, i0 + (uint32_t)e));
-            if (rare(hl.n > TH_CUT)) hl.cut();
+            if (rare(hl.n > TH_CUT)) {
+                hl.cut();
+                th = __builtin_fmaxf(th, key_value(hl.tau + 1));
+            }
             em &= em - 1;
         }
         hm &= hm - 1;

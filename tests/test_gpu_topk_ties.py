@@ -92,3 +92,35 @@ def test_ties_cost_little(dev, N, V, dtype, K):
     tied = median_us(x, K)
     print(f"{plain:.1f} us, ties {tied:.1f} us", flush=True)
     assert tied <= 1.5 * plain
+
+
+def falling(N, V, dtype, dev):
+    """Logits that fall with the index, as of a vocabulary in order of frequency."""
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=dev).manual_seed(V)
+    x = torch.randn((N, V), generator=g, device=dev)
+    return (x - 1.2 * torch.log1p(torch.arange(V, device=dev))).to(t)
+
+
+@pytest.mark.parametrize("V,dtype", [(1000, "f32"), (4100, "f32"), (32000, "f32"), (128256, "f32"),
+                                     (1000, "bf16"), (9000, "bf16"), (60000, "bf16")])
+def test_largest_elements_side_by_side(dev, V, dtype):
+    x = torch.cat([falling(6, V, dtype, dev), falling(6, V, dtype, dev).flip(1),
+                   torch.arange(V, device=dev).to(torch.float32).mul(-8.0 / V)[None].to(
+                       torch.float32 if dtype == "f32" else torch.bfloat16)])
+    for K in (1, 20, 50, 64):
+        print(f"{V} {dtype} K={K}", flush=True)
+        vals, idx = osm.softmax_topk(x, K)
+        torch.cuda.synchronize()
+        v64, z64 = oracle.topk(to_host(x), K, host_dtype(x))
+        assert_topk_equal(to_host(vals), to_host(idx), v64, z64, f"{V} {dtype} K={K}")
+
+
+@pytest.mark.parametrize("N,V,dtype", [(4000, 1000, "f32"), (2000, 60000, "bf16")])
+def test_largest_side_by_side_cost_little(dev, N, V, dtype):
+    """Against ordinary rows: 1.45 times as long with every list sorted in full."""
+    print(f"{N}x{V} {dtype}", flush=True)
+    plain = median_us(synth.logits(N, V, sigma=2.0, seed=1, dtype=dtype, device=dev), 50)
+    side = median_us(falling(N, V, dtype, dev), 50)
+    print(f"{plain:.1f} us, side by side {side:.1f} us", flush=True)
+    assert side <= 1.38 * plain
