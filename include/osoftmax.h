@@ -290,8 +290,9 @@ OSM_API int osm_ref_stream(int op, const void* x, void* y, int64_t bytes, hipStr
 OSM_API int osm_stream_release(hipStream_t stream);
 
 /* Kernel family and parameter softmax_fwd would use for this shape on the
- * current device (for OSM_RESIDENT: OSM_KERNEL_ROWS and the threads per row;
- * for N = 0, which launches nothing, those of one row).  Errors: OSM_EINVAL
+ * current device, with x and y congruent modulo 16 bytes (for OSM_RESIDENT:
+ * OSM_KERNEL_ROWS and the threads per row; for N = 0, which launches nothing,
+ * those of one row).  Errors: OSM_EINVAL
  * for bad sizes, dtype or null outputs; OSM_EUNSUPPORTED for OSM_RESIDENT
  * rows it cannot hold. */
 OSM_API int osm_plan(int64_t N, int64_t V, int dtype, int mode, int* kernel, int64_t* param);

@@ -220,7 +220,9 @@ struct Plan {
     int64_t param;
 };
 
-Plan choose(int64_t N, int64_t V, int dtype, int cus) {
+// vec: x and y are congruent modulo 16 bytes (else rows are taken an element at
+// a time).
+Plan choose(int64_t N, int64_t V, int dtype, int cus, bool vec = true) {
     const int64_t E = elems_per_vec(dtype);
     const int64_t nv = (V + E - 1) / E;  // 16-byte vectors per row
     // Short rows: a lane group per row, sized so each lane has ~2-4 vectors.
@@ -266,8 +268,15 @@ Plan choose(int64_t N, int64_t V, int dtype, int cus) {
     const bool f32 = dtype == OSM_F32;
     const bool busy = f32 || V <= 57344 ? 2 * N >= cus : 4 * N >= 3 * (int64_t)cus;
     const bool even = N <= cus || 5 * N >= 8 * (int64_t)cus;
-    const bool rows = V <= 20480 || (V <= (f32 ? 57344 : 24576) && 8 * N >= 3 * (int64_t)cus) ||
-                      (V <= 131072 && busy && even);
+    bool rows = V <= 20480 || (V <= (f32 ? 57344 : 24576) && 8 * N >= 3 * (int64_t)cus) ||
+                (V <= 131072 && busy && even);
+    // An element at a time a row is bound by the accesses a CU can make, not by
+    // memory, and the split's many workgroups are faster down to 16384 elements
+    // until every CU has a row of more than 6144 vectors' length (x and y apart by
+    // 3 elements, rows / split: bfloat16 64 x 16384 19.2 / 8.8, 192 x 32000 33.7 /
+    // 15.4, 410 x 40000 54.2 / 43.1; binary32 96 x 57344 39.1 / 20.1, 300 x 24576
+    // 34.9 / 23.9; but 256 x 32000 26.2 / 28.0, bfloat16 410 x 57344 47.7 / 58.8).
+    if (!vec) rows = V < 16384 || (rows && nv > 6144 && N >= cus);
     if (N < 2 * (int64_t)cus && rows && nv > 2048 && nv <= 6144) return {OSM_KERNEL_ROWS, 512};
     if (N < 2 * (int64_t)cus && !rows) {
         int64_t S = (want_blocks + N - 1) / N;
@@ -338,7 +347,7 @@ int run_softmax(const void* x, void* y, int64_t N, int64_t V, int dtype, int mod
     int dev = 0;
     DeviceState* ds = device_state(&dev);
     if (!ds) return OSM_EHIP;
-    Plan p = kernel == OSM_KERNEL_AUTO ? choose(N, V, dtype, ds->cus) : Plan{kernel, param};
+    Plan p = kernel == OSM_KERNEL_AUTO ? choose(N, V, dtype, ds->cus, vec) : Plan{kernel, param};
 
     if (p.kernel == OSM_KERNEL_ROWS)
         return hip_status(osm::launch_softmax_rows(x, y, N, V, dtype, mode, (int)p.param, vec,

@@ -57,3 +57,50 @@ def test_lanes_line(N, V, dtype, lanes):
         pick = [0, 1, N // 2, N - 1]
         assert_softmax_close(to_host(y[pick]), oracle.softmax(to_host(x[pick]), host_dtype(x)),
                              f"{N}x{V} {dtype} {mode}")
+
+
+def offset_pair(N, V, dtype):
+    """x and a y that is not congruent with it modulo 16 bytes."""
+    x = synth.logits(N, V, sigma=3.0, seed=V, dtype=dtype, device="cuda")
+    y = torch.empty(N * V + 8, dtype=x.dtype, device="cuda")[3:3 + N * V].view(N, V)
+    return x, y
+
+
+@pytest.mark.parametrize("N,V,dtype", [
+    (2, 16383, "bf16"), (2, 16384, "bf16"), (64, 16385, "f32"), (192, 32000, "bf16"),
+    (255, 24580, "f32"), (256, 24580, "f32"), (300, 24577, "f32"), (410, 49160, "bf16")])
+def test_incongruent_outputs(N, V, dtype):
+    x, y = offset_pair(N, V, dtype)
+    for mode in ("naive", "safe", "online"):
+        print(f"{N}x{V} {dtype} {mode}", flush=True)
+        osm.softmax_fwd(x, y, mode=mode)
+        pick = [0, 1, N // 2, N - 1]
+        assert_softmax_close(to_host(y[pick]), oracle.softmax(to_host(x[pick]), host_dtype(x)),
+                             f"{N}x{V} {dtype} {mode}")
+
+
+def median_us(x, y, **kernel):
+    times = []
+    for _ in range(9):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda._sleep(1 << 19)               # the calls queue up behind it
+        a.record()
+        for _ in range(10):
+            osm.softmax_fwd(x, y, **kernel)
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 100)
+    return sorted(times)[4]
+
+
+@pytest.mark.parametrize("N,V,dtype,S", [(64, 16384, "bf16", 4), (192, 32000, "bf16", 6),
+                                         (96, 57344, "f32", 11)])
+def test_incongruent_outputs_keep_the_split(N, V, dtype, S):
+    """A workgroup per row took about twice the time of split rows here."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the batch sizes stand for 256 CUs")
+    x, y = offset_pair(N, V, dtype)
+    print(f"{N}x{V} {dtype}", flush=True)
+    auto, split = median_us(x, y), median_us(x, y, kernel=osm.KERNEL_SPLIT, param=S)
+    print(f"{auto:.1f} us, split {split:.1f} us", flush=True)
+    assert auto <= 1.3 * split
