@@ -270,6 +270,11 @@ Plan choose(int64_t N, int64_t V, int dtype, int cus, bool vec = true) {
     const bool even = N <= cus || 5 * N >= 8 * (int64_t)cus;
     bool rows = V <= 20480 || (V <= (f32 ? 57344 : 24576) && 8 * N >= 3 * (int64_t)cus) ||
                 (V <= 131072 && busy && even);
+    // With half to five eighths of the CUs busy, binary32 rows of 48 K to 64 K
+    // elements lose more at some lengths than they gain at others (rows / split: 128 x 50000 16.7 / 12.8, x 50257 16.1 / 14.2, x 53000 14.4 /
+    // 14.9, x 57344 15.2 / 13.1; 160 x 50000 18.4 / 16.5, x 53000 16.8 / 17.5, x
+    // 57344 18.8 / 17.3; but 112 x 50000 11.6 / 13.0, 192 x 57344 20.4 / 23.7).
+    if (f32 && V > 49152 && V <= 65536 && 2 * N >= cus && 8 * N <= 5 * (int64_t)cus) rows = false;
     // An element at a time a row is bound by the accesses a CU can make, not by
     // memory, and the split's many workgroups are faster down to 16384 elements
     // until every CU has a row of more than 6144 vectors' length (x and y apart by

@@ -16,7 +16,9 @@ R, S = osm.KERNEL_ROWS, osm.KERNEL_SPLIT
 
 @pytest.mark.parametrize("N,V,dtype,kernel", [
     (2, 16384, "f32", R), (2, 20480, "bf16", R), (2, 20481, "f32", S), (95, 20481, "bf16", S),
-    (96, 20481, "f32", R), (96, 57344, "f32", R), (96, 57345, "f32", S), (128, 57345, "f32", R),
+    (96, 20481, "f32", R), (96, 57344, "f32", R), (96, 57345, "f32", S), (127, 50000, "f32", R),
+    (128, 49152, "f32", R), (128, 49153, "f32", S), (160, 65536, "f32", S), (160, 65537, "f32", R),
+    (161, 57345, "f32", R),
     (256, 131071, "f32", R), (257, 57345, "f32", S), (128, 131073, "f32", S),
     (96, 24576, "bf16", R), (96, 24577, "bf16", S), (128, 24577, "bf16", R), (191, 57345, "bf16", S),
     (192, 57345, "bf16", R), (300, 24577, "bf16", S), (410, 24577, "bf16", R), (511, 16385, "bf16", R),
@@ -91,6 +93,19 @@ def median_us(x, y, **kernel):
         b.synchronize()
         times.append(a.elapsed_time(b) * 100)
     return sorted(times)[4]
+
+
+@pytest.mark.parametrize("N,V,S", [(128, 50000, 8), (144, 50000, 8), (128, 57344, 8)])
+def test_half_the_chip_busy(N, V, S):
+    """A workgroup per row took up to 1.3 times the time of split rows here."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the batch sizes stand for 256 CUs")
+    x = synth.logits(N, V, sigma=3.0, seed=V, device="cuda")
+    y = torch.empty_like(x)
+    print(f"{N}x{V}", flush=True)
+    auto, split = median_us(x, y), median_us(x, y, kernel=osm.KERNEL_SPLIT, param=S)
+    print(f"{auto:.1f} us, split {split:.1f} us", flush=True)
+    assert osm.plan(N, V)[0] == osm.KERNEL_SPLIT and auto <= 1.1 * split
 
 
 @pytest.mark.parametrize("N,V,dtype,S", [(64, 16384, "bf16", 4), (192, 32000, "bf16", 6),
