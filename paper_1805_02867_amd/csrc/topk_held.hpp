@@ -238,7 +238,9 @@ __device__ __forceinline__ uint64_t held_finish(uint64_t (*lists)[TH_LIST], cons
         }
         return i < total ? lists[w][j] : 0ull;
     };
-    if (W > 1 && rare(total > 64 && total <= TH_LIST)) {  // thinned out ahead of the sort
+    // thinned out ahead of the sort, where that saves one (a bound leaves up to
+    // K + K / 4 + 1 keys, more than one sort's for K > 50)
+    if (W > 1 && rare(total > (K <= 50 ? 64 : 128) && total <= TH_LIST)) {
         const uint64_t k[3] = {at(lane), at(lane + 64), at(lane + 128)};
         uint32_t lo;
         const int n = thin_keys(k, K, lists[0], &lo);
