@@ -420,12 +420,18 @@ Plan choose_topk_stream(int64_t N, int64_t V, int K, int cus, int64_t min_chunk 
 //    wavefronts does, against streaming the row by one wavefront (4000 x 10000
 //    binary32 top-5 / top-50: 28.2 / 29.7 against 31.0 / 37.2; 4000 x 32000
 //    bfloat16 43.3 / 46.7 against 52.4 / 67.8; 16000 x 32000 binary32 292 / 328
-//    against 303 / 330) and against splitting it (64 x 32000 binary32 8.3 / 9.9
-//    against 9.8 / 11.4).  Large batches of bfloat16 rows past 4096 vectors
+//    against 303 / 330; 4000 x 25000 top-5 / top-30 63.5 / 63.8 against 63.9 /
+//    66.3) and against splitting it (64 x 32000 binary32 8.3 / 9.9 against
+//    9.8 / 11.4).  Large batches of bfloat16 rows past 4096 vectors
 //    stream (4000 x 50000 top-5: 69.1 against 73.9: half the bytes for the same
-//    arithmetic, which a held row does not overlap with its loads), and a few
-//    rows past 4096 vectors at small K split (1 x 65000 bfloat16 top-5: 6.9
-//    against 8.0; top-50 9.9 against 9.3);
+//    arithmetic, which a held row does not overlap with its loads), and so do, at
+//    large K, binary32 rows of 13 to 15 vectors a lane that load 16 (top-5 /
+//    top-30 / top-64, streamed against held: 4000 x 27000 68.5 / 70.5 / 77.3
+//    against 69.0 / 74.7 / 84.9, x 30000 75.3 / 77.1 / 84.3 against 75.4 / 78.6 /
+//    88.7; but 2100 x 27000, a few rows into another round of streams, 47.1 /
+//    49.2 / 57.0 against 40.6 / 43.9 / 51.4, and 1024 x 27000 22.3 / 29.4 / 39.0
+//    against 21.0 / 22.9 / 25.8).  A few rows past 4096 vectors at small K split
+//    (1 x 65000 bfloat16 top-5: 6.9 against 8.0; top-50 9.9 against 9.3);
 //  * longer rows are streamed or split, the chunks with at least 2048 vectors
 //    (16 x 128256 bfloat16 top-5: 9.4 in 8 chunks, 12.4 in 31), or 1024 for a
 //    few rows (1 x 128256 bfloat16 top-5: 8.2 in 7 chunks, 7.1 in 31);
@@ -437,8 +443,9 @@ Plan choose_topk(int64_t N, int64_t V, int dtype, int K, int cus) {
     const bool many = N >= 4 * (int64_t)cus;
     if (V <= 1536 || (many && nv <= 1024) || N * 256 > kMaxThreads) return {OSM_KERNEL_ROWS, 64};
     if (nv <= 4096) return {OSM_KERNEL_ROWS, 256};
-    if (nv <= 8192 && (many ? dtype == OSM_F32 || N < 8 * (int64_t)cus : N >= 16 || K > 8))
-        return {OSM_KERNEL_ROWS, 256};
+    const bool stream = dtype == OSM_F32 ? K > 20 && nv > 6656 && nv <= 7800 && N >= 11 * (int64_t)cus
+                                         : N >= 8 * (int64_t)cus;
+    if (nv <= 8192 && (many ? !stream : N >= 16 || K > 8)) return {OSM_KERNEL_ROWS, 256};
     return choose_topk_stream(N, V, K, cus, (N <= 8 ? 1024 : 2048) * E);
 }
 

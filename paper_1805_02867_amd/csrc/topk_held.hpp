@@ -647,7 +647,7 @@ constexpr int held_waves() {
     const bool more = Vec<T>::N == 8 && (W == 8 || PART);  // bfloat16 widens to twice as many
     return R <= 6    ? (PART ? 7 : 8)
            : R <= 8  ? (more ? 6 : PART ? 7 : 8)
-           : R <= 12 ? (more || PART ? 5 : 6)
+           : R <= 13 ? (more || PART ? 5 : 6)
                      : (more && W == 4 ? 4 : 5);
 }
 
@@ -813,7 +813,11 @@ hipError_t launch_merge_held(const uint64_t* pkeys, const MD* pmd, float* vals, 
 }
 
 // Vectors per lane: the smallest of 1, 2, 3, 4, 6, 8, 12, 16 that holds the
-// row's `nv` vectors (a lane's spare vectors cost a masked load each).
+// row's `nv` vectors (a lane's spare vectors cost a masked load each); for
+// binary32 by eight wavefronts also 13, the most that leaves three workgroups a
+// CU their registers (4000 x 25000 top-5 / top-30 / top-64 66.7 / 72.2 / 83.0 us
+// with 16, 63.5 / 63.8 / 66.0 with 13; 14 in as many registers spills, 15 and 16
+// are level).
 template <typename T, int W, int VAR, bool PART>
 hipError_t launch_held_w(const TopkLaunch& a, int64_t nv, uint64_t* pkeys, MD* pmd) {
     const int64_t r = (nv + 64 * W - 1) / (64 * W);
@@ -831,6 +835,7 @@ hipError_t launch_held_w(const TopkLaunch& a, int64_t nv, uint64_t* pkeys, MD* p
     else if (r <= 6) OSM_HELD(6);
     else if (r <= 8) OSM_HELD(8);
     else if (r <= 12) OSM_HELD(12);
+    else if (W == 8 && Vec<T>::N == 4 && r <= 13) OSM_HELD((W == 8 && Vec<T>::N == 4 ? 13 : 16));
     else if (r <= TH_RMAX) OSM_HELD(16);
     else return hipErrorInvalidValue;
 #undef OSM_HELD

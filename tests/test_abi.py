@@ -251,6 +251,20 @@ def test_plans_of_an_empty_batch(V):
             assert osm.topk_plan(0, V, K, dtype=dt) == osm.topk_plan(1, V, K, dtype=dt)
 
 
+def test_topk_plan_streams_part_filled_rows():
+    """binary32 rows that load 16 vectors a lane and hold 13 to 15: streamed at
+    large K and batches, where holding them is slower."""
+    import torch
+    if torch.cuda.is_available() and torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the batch sizes stand for 256 CUs")
+    held, streamed = (osm.KERNEL_ROWS, 256), (osm.KERNEL_ROWS, 64)
+    for N, V, K, want in ((4000, 26624, 64, held), (4000, 26628, 21, streamed),
+                          (4000, 31200, 64, streamed), (4000, 31204, 64, held),
+                          (4000, 28000, 20, held), (2815, 28000, 30, held),
+                          (2816, 28000, 30, streamed), (1024, 28000, 64, held)):
+        assert osm.topk_plan(N, V, K) == want, (N, V, K)
+
+
 @pytest.mark.parametrize("dtype,V", [(osm.F32, 4100), (osm.BF16, 8200)])
 def test_topk_plan_fits_one_launch(dtype, V):
     """A launch takes fewer than 2^32 threads: the rows of the largest batches
