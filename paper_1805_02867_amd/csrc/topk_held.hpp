@@ -851,8 +851,14 @@ bool launch_topk_held(const TopkLaunch& a, uint64_t* pkeys, MD* pmd, hipError_t*
         // Chunks of eight wavefronts: two workgroups a CU are resident.  With
         // more of them than that, streamed chunks overlap the next one's loads
         // better than the selection costs at small K (400 x 50000 binary32 in
-        // 800 chunks, top-1: 21.8 us streamed, 22.7 held; top-5 26.1 and 25.1).
-        const bool eight = a.N * a.S <= 2 * (int64_t)a.cus || a.K > 4;
+        // 800 chunks, top-1: 21.8 us streamed, 22.7 held; top-5 26.1 and 25.1),
+        // most where the second round is short (top-5, streamed / held: 300 x
+        // 50257 21.2 / 21.6, 350 x 50257 21.7 / 22.5, 300 x 60000 22.1 / 23.8;
+        // but 257 x 50257 18.4 / 17.5, 300 x 40000, whose chunks leave room for
+        // three workgroups, 17.6 / 14.4, and top-16 300 x 50257 23.9 / 22.7).
+        const int64_t n = a.N * a.S, two = 2 * (int64_t)a.cus;
+        const bool few = nv > 512 * 12 && 10 * n > 11 * two && 2 * n < 3 * two;
+        const bool eight = n <= two || a.K > (few ? 8 : 4);
         if (nv <= 256 * TH_RMAX) *e = launch_held_w<T, 4, VAR, true>(a, nv, pkeys, pmd);
         else if (nv <= 512 * TH_RMAX && eight) *e = launch_held_w<T, 8, VAR, true>(a, nv, pkeys, pmd);
         else return false;

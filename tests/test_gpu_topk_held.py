@@ -90,6 +90,19 @@ def test_plain_topk_skips_nan(dev, dtype):
             assert (v[:z.size] == xh[r][z]).all() and np.isnan(v[z.size:]).all(), (V, r)
 
 
+@pytest.mark.parametrize("N,V,K", [(300, 50257, 5), (300, 50257, 9), (350, 65000, 8), (281, 49200, 8),
+                                   (282, 49200, 8), (383, 49200, 5), (384, 49200, 5), (300, 40000, 5)])
+def test_second_round_of_chunks(dev, N, V, K):
+    """Two chunks a row, a little more of them than fit on the chip at once."""
+    print(f"{N}x{V} K={K}", flush=True)
+    x = synth.logits(N, V, sigma=2.0, seed=V, device=dev)
+    vals, idx = osm.softmax_topk(x, K)
+    torch.cuda.synchronize()
+    pick = [0, 1, N // 2, N - 1]
+    v64, z64 = oracle.topk(to_host(x[pick]), K, host_dtype(x))
+    assert_topk_equal(to_host(vals)[pick], to_host(idx)[pick], v64, z64, f"{N}x{V} K={K}")
+
+
 def median_us(x, K):
     times = []
     for _ in range(9):
