@@ -1,6 +1,6 @@
 """The 256 x 256 projection core (calls of 512 tiles and more, and the fused
 top-k past 128 rows) at the edges of its K steps and tiles, and the fused
-epilogue on logits in rising and falling order and all equal.  Every product
+epilogue on logits in rising and falling order, all equal and infinite.  Every product
 and sum is exact in binary32 whatever its order, so logits must equal the
 binary64 ones bit for bit and top-k indices the oracle's."""
 import numpy as np
@@ -84,3 +84,43 @@ def test_small_batch_tile_heights(dev, V, K):
     for N, H in ((1, 72), (64, 1032)):
         check_topk(*exact_inputs(N, H, V, seed=N + V + H + K, dev=dev), min(K, V),
                    f"fused N={N} H={H} V={V} K={K}")
+
+
+@pytest.mark.parametrize("K", [9, 12, 16])
+@pytest.mark.parametrize("N,H,V", [
+    (257, 2048, 33000), (1100, 2056, 16001),   # a tile a workgroup, ragged both ways
+    (600, 2048, 30001),                        # two tiles a workgroup
+    (256, 2048, 65537), (256, 2048, 65536),    # one strip: on both sides of the layout's line
+    (1100, 2040, 16001)])                      # H below it
+def test_lists_of_16_on_the_two_group_core(dev, N, H, V, K):
+    check_topk(*exact_inputs(N, H, V, seed=N + V + K, dev=dev), K, f"fused N={N} H={H} V={V} K={K}")
+
+
+@pytest.mark.parametrize("N,H,V,K", [
+    (40, 64, 9000, 1), (40, 64, 9000, 8), (40, 64, 9000, 16),          # tiles of 64 and 256
+    (40, 72, 45000, 5), (100, 64, 9000, 5), (100, 64, 9000, 16),       # of 128; 128 rows a strip
+    (200, 64, 9000, 1), (200, 64, 9000, 8), (1100, 64, 9000, 16), (257, 2048, 33000, 12)])
+def test_infinite_logits(dev, N, H, V, K):
+    """-infinity is passed over and adds nothing; +infinity comes first, in index
+    order, and makes every probability of its row NaN, as inf - inf is."""
+    h, w = exact_inputs(N, H, V, seed=N + V + K, dev=dev)
+    h[:, 0] = 0.5
+    v = torch.arange(V, device=dev)
+    w[(v < 700) | (v % 3 == 0) | (v > V - 70), 0] = float("-inf")
+    print(f"-inf N={N} H={H} V={V} K={K}", flush=True)
+    vals, idx = osm.proj_softmax_topk(h, w, K)
+    torch.cuda.synchronize()
+    x = to_host(logits64(h, w))
+    v64, z64 = oracle.topk(x, K, "f64")
+    assert np.array_equal(to_host(idx), z64)
+    assert (rel_err_f32(to_host(vals), v64) <= 1).all()
+
+    w[[701, 702, V // 2, V - 71], 0] = float("inf")
+    w[1000:1040:2, 0] = float("inf")                   # more than K of them in a lane or two
+    print(f"+inf N={N} H={H} V={V} K={K}", flush=True)
+    vals, idx = osm.proj_softmax_topk(h, w, K)
+    torch.cuda.synchronize()
+    x = to_host(logits64(h, w))
+    z = np.argsort(-x, axis=1, kind="stable")[:, :K]
+    assert np.array_equal(to_host(idx), z)
+    assert np.isnan(to_host(vals)).all()

@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N,K,H,V", [
     (1, 5, 4096, 49153), (64, 16, 4096, 49153),  # 384 MiB and one row of 8 KiB
-    (100, 5, 4096, 49153), (128, 16, 4096, 49153), (200, 8, 4096, 49153), (256, 12, 4096, 49153),
+    (100, 5, 4096, 49153), (128, 16, 4096, 49153), (200, 8, 4096, 49153),
+    (256, 12, 2048, 98305),                      # lists of 16 in one strip of 256
+    (256, 12, 4096, 49153),                      # in two strips of 128: the default policy
     (64, 5, 4088, 49300), (64, 12, 4104, 49300),  # rows of part lines: the default policy
 ])
 def test_large_vocabulary(N, K, H, V):
