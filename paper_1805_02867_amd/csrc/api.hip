@@ -235,8 +235,10 @@ Plan choose(int64_t N, int64_t V, int dtype, int cus, bool vec = true) {
     // 3.20; bfloat16 64 x 2000 4.4 -> 3.0, 200 x 8192 8.2 -> 3.8), then two
     // wavefronts (binary32 800 x 4096 6.9 -> 4.9, but 1024 x 2000 5.08 -> 5.14).
     // Larger batches keep a wavefront, but for bfloat16 rows of 513 to 768
-    // vectors (4000 x 5000 18.8 -> 15.6, 32768 x 5000 139 -> 115; 3000 x 2400
-    // 6.9 -> 7.7).
+    // vectors in batches of eight rows a CU and more (4000 x 5000 18.8 -> 15.6,
+    // 32768 x 5000 139 -> 115; 3000 x 2400 6.9 -> 7.7).  Between four and eight
+    // rows a CU two wavefronts gain at some lengths and lose at others (1500 x
+    // 5000 9.2 -> 8.3, 1500 x 6144 8.5 -> 8.6, 1800 x 6144 8.6 -> 9.1).
     const int64_t c = cus;
     if (nv <= 128) {  // bfloat16: 200 x 1000 4.4 -> 3.0, but 512 x 600 3.40 -> 3.55
         if (dtype != OSM_F32 && nv > 96 && N <= 2 * c) return {OSM_KERNEL_ROWS, 128};
@@ -392,10 +394,13 @@ int run_softmax(const void* x, void* y, int64_t N, int64_t V, int dtype, int mod
 // 34.5 us in 510 workgroups against 41.8 in 520); otherwise a workgroup (four
 // wavefronts) per row.
 //
-// The chunk count is also capped so that a row's S * K partial keys fit the
-// merge's single register batch (512 keys; a larger merge goes through the
-// queue and its repeated selections: 4 x 10^6 top-5 took 20.8 us at 128
-// chunks against 15.7 at 52), and chunks keep at least `min_chunk` elements.
+// The chunk count is also capped so that a row's S * K partial keys fit one
+// batch of a wavefront's merge (512 keys), and chunks keep at least `min_chunk`
+// elements.  The cap is low for K > 15: the whole workgroup merges more keys as
+// well, and longer chunks no longer fit in registers (10 x 10^6 binary32, this
+// plan / 34 / 51 chunks: top-15 16.5 / 16.4 / 17.8 us, top-30 25.8 / 18.1 / 17.9,
+// top-50 34.9 / 19.6 / 18.7, top-64 44.7 / 27.4 / 31.7; bfloat16 top-30 14.1 /
+// 15.2 / 16.3).
 Plan choose_topk_stream(int64_t N, int64_t V, int K, int cus, int64_t min_chunk = 4096) {
     if (N >= 4 * (int64_t)cus || V <= 1536) return {OSM_KERNEL_ROWS, 64};
     if (N < 2 * (int64_t)cus && V >= 8192) {
@@ -571,12 +576,13 @@ int run_topk(const void* x, void* y, float* vals, int32_t* idx, int64_t N, int64
 }
 
 // ---------------------------------------------------------------- projection
-constexpr int64_t kProjTile = 128;     // smallest tile edge of the projection kernels
+constexpr int64_t kProjTile = 128;     // tile edge of the largest grids
 constexpr int64_t kProjMaxH = 1 << 20;  // 32-bit load offsets within a tile
 
 // Arguments shared by the projection entry points; OSM_OK if valid.
 int check_proj(const void* h, const void* w, int64_t N, int64_t H, int64_t V) {
     // the tile grid is one-dimensional: (N / 128) * (V / 128) workgroups < 2^31
+    // (the tiles with shorter edges take a single strip of up to 64 rows)
     if (N < 0 || N > 65535 * kProjTile || V < 1 || V > kMaxDim || H < 8 || H > kProjMaxH ||
         H % 8 != 0 ||
         ((N + kProjTile - 1) / kProjTile) * ((V + kProjTile - 1) / kProjTile) > (kMaxDim - 7))

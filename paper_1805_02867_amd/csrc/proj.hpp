@@ -282,7 +282,7 @@ __device__ __forceinline__ void pj_run(const uint16_t* __restrict__ X, int64_t n
 // a wavefront on it.  In pj_run all eight read after each barrier together and
 // the matrix cores wait for the first fragments.  Measured: matrix cores busy
 // 77% of the cycles against 60%; logits of 4000 x 4096 x 32000 977 -> 893 us,
-// 512 x 4096 x 128256 545 -> 482 (1.12 PF/s), 4000 x 4096 x 128256 3825 -> 3490
+// 512 x 4096 x 128256 517 -> 482 (1.12 PF/s), 4000 x 4096 x 128256 3825 -> 3490
 // (1.20 PF/s).  What bounds it now is power (the clock settles near 1.6 GHz)
 // and the loads' way into the LDS: without the loads it runs at 1.45 PF/s,
 // without any wait for them no faster than with.

@@ -3,8 +3,8 @@
 // the registers.
 //
 // What bounds these shapes is not bandwidth but the chain from the last load
-// to the outputs, so the chain is kept short and the code small (7-14 KB a row
-// kernel, 26-30 KB a split one, against 60-165 KB for the streaming kernels of
+// to the outputs, so the chain is kept short and the code small (8-25 KB a row
+// kernel, 35-47 KB a split one, against 60-172 KB for the streaming kernels of
 // topk.hpp, whose first pass through the code costs more than the work on a
 // short row).  Measured against those kernels, warm, back to back:
 //   4000 x 1000 binary32 top-5    9.9 -> 6.5 us   (16 MB; a launch is ~2.5 us)
@@ -27,8 +27,11 @@
 //     pass for K = 50.
 //  3. The candidates at or above the threshold are appended to a small list of
 //     keys in LDS, in rounds that take one vector per lane.  A list of more
-//     than 128 keys (ties, or a threshold low among few groups) is cut back to
-//     its K largest, whose last key is then the exact filter.
+//     than 128 keys (a threshold low among few groups) is thinned to the keys
+//     that reach a bound of its own.  Where the search for the threshold ends
+//     at a value that many groups share (rows of ties), the elements of that
+//     value are taken in index order instead, as many as are needed, and only
+//     larger ones are looked for.
 //  4. One bitonic sort of the list (of 16 keys when no more are left) gives
 //     the outputs in key order.
 //
@@ -41,7 +44,7 @@
 namespace osm {
 
 constexpr int TH_LIST = 192;  // slots of a wavefront's key list: up to 128, and 64 appended
-constexpr int TH_CUT = 128;   // a longer list is cut back to its K largest
+constexpr int TH_CUT = 128;   // a longer list is thinned
 
 // Order-preserving image of a value: a larger word means a larger value.
 // -0.0 and +0.0 have the same image.
@@ -767,8 +770,8 @@ __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W, (held_waves<T, W, R, PA
     held_end<W, VAR, PART, GRAN>(sm, hl, md, vals, idx, pkeys, pmd, ctr, row, vr, segs, K);
 }
 
-// Second stage of a two-kernel split: a row's n = S K partial keys and S pairs
-// by W wavefronts (W = 1: four rows per workgroup), R keys a lane at a time.
+// Second kernel of the projection with top-k: a row's n = S K partial keys and S
+// pairs by W wavefronts (W = 1: four rows per workgroup), R keys a lane at a time.
 template <int VAR, int W, int R>
 __global__ __launch_bounds__(W == 1 ? TK_BLOCK : 64 * W) void topk_merge_held(
     const uint64_t* __restrict__ pkeys, const MD* __restrict__ pmd, float* __restrict__ vals,
