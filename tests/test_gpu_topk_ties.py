@@ -27,7 +27,7 @@ def tied_rows(V, dtype, dev, seed):
 
     def pick(levels):
         return torch.randint(0, levels, (V,), generator=g, device=dev)
-    x = torch.empty((9, V), dtype=t, device=dev)
+    x = torch.empty((10, V), dtype=t, device=dev)
     x[0] = -1.5                                          # one value
     x[1] = (pick(2) * 2 - 1) * 0.0                       # +0 and -0, which are equal
     x[2] = pick(7) * 0.5 - 2
@@ -41,6 +41,7 @@ def tied_rows(V, dtype, dev, seed):
     x[7, :V // 2] = -8.0                                 # ties in the second half
     x[8] = torch.finfo(t).min / 4                        # a finite mask, and half of the row
     x[8, ::2] = 0.25
+    x[9] = pick(30) * 0.25
     return x
 
 
@@ -92,6 +93,20 @@ def test_ties_cost_little(dev, N, V, dtype, K):
     tied = median_us(x, K)
     print(f"{plain:.1f} us, ties {tied:.1f} us", flush=True)
     assert tied <= 1.5 * plain
+
+
+@pytest.mark.parametrize("N,V,dtype,levels", [(4000, 4000, "f32", 7), (2000, 60000, "bf16", 100)])
+def test_sparser_ties_cost_little(dev, N, V, dtype, levels):
+    """One element in 7, and in 100, equal to the largest: the first vectors of a
+    team hold fewer than 50, the next few do (1.9 times as long without them)."""
+    x = synth.logits(N, V, sigma=2.0, seed=1, dtype=dtype, device=dev)
+    print(f"{N}x{V} {dtype} {levels} levels", flush=True)
+    plain = median_us(x, 50)
+    g = torch.Generator(device=dev).manual_seed(V)
+    x.copy_(torch.randint(0, levels, (N, V), generator=g, device=dev) * 0.0625)
+    tied = median_us(x, 50)
+    print(f"{plain:.1f} us, ties {tied:.1f} us", flush=True)
+    assert tied <= 1.45 * plain
 
 
 def falling(N, V, dtype, dev):
