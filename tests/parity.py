@@ -85,3 +85,20 @@ def assert_topk_equal(vals: np.ndarray, idx: np.ndarray, v64: np.ndarray, z64: n
         r, c = np.unravel_index(np.nanargmax(s), s.shape)
         raise AssertionError(f"{what}: top-k value error {np.nanmax(s):.3g} x tolerance at "
                              f"row {r} slot {c}: gpu {vals[r, c]!r} oracle {v64[r, c]!r}")
+
+
+def best_us(call, batches: int = 9, calls: int = 10) -> float:
+    """GPU time of one call, in us: the fastest of `batches` batches of
+    back-to-back calls, each queued behind a short spin kernel so that the
+    events bracket GPU time."""
+    times = []
+    for _ in range(batches):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda._sleep(1 << 19)
+        a.record()
+        for _ in range(calls):
+            call()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / calls)
+    return min(times)

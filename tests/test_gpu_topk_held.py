@@ -9,7 +9,7 @@ import torch
 import oracle
 import paper_1805_02867_amd as osm
 from paper_1805_02867_amd import synth
-from parity import assert_topk_equal, host_dtype, to_host
+from parity import assert_topk_equal, best_us, host_dtype, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -103,26 +103,14 @@ def test_second_round_of_chunks(dev, N, V, K):
     assert_topk_equal(to_host(vals)[pick], to_host(idx)[pick], v64, z64, f"{N}x{V} K={K}")
 
 
-def median_us(x, K):
-    times = []
-    for _ in range(9):
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        torch.cuda._sleep(1 << 19)               # the calls queue up behind it
-        a.record()
-        for _ in range(10):
-            osm.softmax_topk(x, K)
-        b.record()
-        b.synchronize()
-        times.append(a.elapsed_time(b) * 100)
-    return float(np.median(times))
-
-
 @pytest.mark.parametrize("K", [30, 64])
 def test_thirteen_vectors_a_lane(dev, K):
     """Rows a little past 12 vectors a lane took 1.2 to 1.35 times the time of
     those with 12, since they loaded 16."""
     print(f"K={K}", flush=True)
-    twelve = median_us(synth.logits(4000, 24576, sigma=2.0, seed=1, device=dev), K)
-    more = median_us(synth.logits(4000, 25000, sigma=2.0, seed=1, device=dev), K)
+    x = synth.logits(4000, 24576, sigma=2.0, seed=1, device=dev)
+    twelve = best_us(lambda: osm.softmax_topk(x, K))
+    x = synth.logits(4000, 25000, sigma=2.0, seed=1, device=dev)
+    more = best_us(lambda: osm.softmax_topk(x, K))
     print(f"{twelve:.1f} us, {more:.1f} us", flush=True)
     assert more <= 1.14 * twelve
