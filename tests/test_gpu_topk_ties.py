@@ -1,7 +1,7 @@
 """Top-k of rows in which many elements share one value (rows of one value,
 coarse grids, masks): the lowest indices win, as the oracle has it, whichever
-wavefront, vector or scalar end of the row they lie in; and such rows take
-little longer than rows without ties."""
+wavefront, vector or scalar end of the row they lie in; and of rows whose
+largest elements lie side by side.  Both take little longer than other rows."""
 import pytest
 import torch
 
